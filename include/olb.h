@@ -143,7 +143,9 @@ olb_status olb_wall_density(olb_ctx* c, double* nw_lo, double* nw_hi);
 
 /* Block height of the stage kernel: 8 (default) or 16 waves per workgroup,
  * or 12 with FP32 storage (OLB_E_ARG otherwise); each workgroup updates
- * 63 x by nodes.  Results do not depend on it. */
+ * 63 x by nodes.  Lattices and batches too small to fill the GPU with such
+ * tiles take a kernel with 16 x 8 tiles instead, unless this call has chosen
+ * a height.  Results do not depend on either (bitwise). */
 olb_status olb_set_tile(olb_ctx* c, int32_t by);
 /* FP32 departure storage keeps f - rho_ref b_kx b_ky, with the per-axis base
  * b = w (1 + h(0, T - 1)) of the equilibrium at rest and temperature T
@@ -162,8 +164,9 @@ olb_status olb_set_base_temperature(olb_ctx* c, double T);
  * (bitwise).  OLB_E_ARG outside 0..1024. */
 olb_status olb_set_tile_order(olb_ctx* c, int32_t strip);
 
-/* Number of stage-kernel launches olb_step enqueues per RK-3 step (3), and
- * of wall-ghost launches (3 with walls, else 0). */
+/* Number of stage launches olb_step enqueues per RK-3 step (3), and of
+ * wall-ghost updates (3 with walls, else 0; where the lattice takes 16 x 8
+ * tiles they are part of the stage launches). */
 olb_status olb_launch_counts(const olb_ctx* c, int32_t* stage, int32_t* walls);
 
 const char* olb_last_error(const olb_ctx* c);

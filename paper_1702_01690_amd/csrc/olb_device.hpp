@@ -76,9 +76,13 @@ struct WallBatchArgs {
 // Tile geometry of the stage kernel: 64 lanes across x produce 63 cells, BY
 // waves across y produce BY rows.
 constexpr int TILE_X = 63;
+// Tiles of the split stage kernel (olb_split.hpp).
+constexpr int SPLIT_X = 16, SPLIT_Y = 8;
 
 // One workgroup per tile of the batch's tile queue.
 hipError_t launch_stage(const BatchArgs& a, int real_bytes, int by, bool walls, bool xspec, hipStream_t s);
+// The same with 16 x 8 tiles, wall ghosts included (no launch_walls).
+hipError_t launch_split(const BatchArgs& a, int real_bytes, bool walls, bool xspec, hipStream_t s);
 // wall_blocks: sum over instances of ceil(nx / 64).
 hipError_t launch_walls(const WallBatchArgs& a, int real_bytes, int wall_blocks, hipStream_t s);
 // f = f^eq(n, u, T) from device fields [4][ny][nx]; also writes the carry.

@@ -26,8 +26,17 @@
 #include "olb_device.hpp"
 #include "olb_feq.hpp"
 
+// Every multiply-add of the update is written out as a fused one, and the
+// compiler forms no others: the stage kernels, the wall kernel and the set-up
+// kernels share these functions, and a node gets the same bits from whichever
+// of them computes it.
+#pragma clang fp contract(off)
+
 namespace olbk {
 using namespace olbc;
+
+__device__ __forceinline__ double fmadd(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
 // Global-memory views of pointers that reach a kernel through a descriptor
 // in memory (the compiler cannot prove their address space and would emit
@@ -218,12 +227,12 @@ __device__ __forceinline__ void sums25(const Real* f, double rho0, double tref, 
       rs[ky] += v;
     }
   n = (cs[0] + cs[4]) + (cs[1] + cs[3]) + cs[2];
-  jx = R4 * (cs[4] - cs[0]) + R3 * (cs[3] - cs[1]);
-  jy = R4 * (rs[4] - rs[0]) + R3 * (rs[3] - rs[1]);
-  e = (R4 * R4) * ((cs[0] + cs[4]) + (rs[0] + rs[4])) + (R3 * R3) * ((cs[1] + cs[3]) + (rs[1] + rs[3]));
+  jx = fmadd(R4, cs[4] - cs[0], R3 * (cs[3] - cs[1]));
+  jy = fmadd(R4, rs[4] - rs[0], R3 * (rs[3] - rs[1]));
+  e = fmadd(R4 * R4, (cs[0] + cs[4]) + (rs[0] + rs[4]), (R3 * R3) * ((cs[1] + cs[3]) + (rs[1] + rs[3])));
   if (std::is_same<Real, float>::value) {
     n += rho0;
-    e += 2.0 * rho0 * tref;
+    e = fmadd(2.0 * rho0, tref, e);
   }
 }
 
@@ -244,9 +253,9 @@ __device__ __forceinline__ void feq25(double n, double ux, double uy, double T, 
       const double w = Wk[kx] * Wk[ky];
       if (std::is_same<Real, float>::value) {
         const double dn = n - rho0;
-        out[5 * ky + kx] = (Real)(w * (dn * (1.0 + hx[kx]) * (1.0 + hy[ky]) +
-                                      rho0 * ((hx[kx] - h0[kx]) * (1.0 + hy[ky]) +
-                                              (1.0 + h0[kx]) * (hy[ky] - h0[ky]))));
+        out[5 * ky + kx] = (Real)(w * fmadd(dn * (1.0 + hx[kx]), 1.0 + hy[ky],
+                                            rho0 * fmadd(hx[kx] - h0[kx], 1.0 + hy[ky],
+                                                         (1.0 + h0[kx]) * (hy[ky] - h0[ky]))));
       } else {
         out[5 * ky + kx] = (Real)(n * (Wk[kx] * (1.0 + hx[kx])) * (Wk[ky] * (1.0 + hy[ky])));
       }
@@ -256,7 +265,12 @@ __device__ __forceinline__ void feq25(double n, double ux, double uy, double T, 
 __device__ __forceinline__ double delta_p(double n, double T, double a, double b) {
   // Delta p = p^i - p^w = nT - [nT/(1 - bn) - a n^2]
   const double nT = n * T;
-  return nT - nT / (1.0 - b * n) + a * n * n;
+  return fmadd(a * n, n, nT - nT / fmadd(-b, n, 1.0));
+}
+
+// T of a node from e = sum |p|^2 f, 1/n and u
+__device__ __forceinline__ double temperature(double e, double inv_n, double ux, double uy) {
+  return 0.5 * fmadd(-uy, uy, fmadd(-ux, ux, e * inv_n));
 }
 
 // Running moment sums n = sum f, j = sum p f, e = sum |p|^2 f of a node's
@@ -274,14 +288,14 @@ struct MomSum {
     const double px = Rk[kx], py = Rk[ky];
     r = kx == 0 ? v : r + v;
     if (kx != 2) {
-      jx += px * v;
-      e += (px * px) * v;
+      jx = fmadd(px, v, jx);
+      e = fmadd(px * px, v, e);
     }
     if (kx == 4) {
       n += r;
       if (ky != 2) {
-        jy += py * r;
-        e += (py * py) * r;
+        jy = fmadd(py, r, jy);
+        e = fmadd(py * py, r, e);
       }
     }
   }
@@ -294,12 +308,12 @@ __device__ __forceinline__ void carry_finish(const MomSum& s, double rho0, doubl
   double n = s.n, jx = s.jx, jy = s.jy, e = s.e;
   if (F32) {
     n += rho0;
-    e += 2.0 * rho0 * tref;
+    e = fmadd(2.0 * rho0, tref, e);
   }
   const double in = 1.0 / n;
   const double vx = jx * in, vy = jy * in;
   n_out = n;
-  dp_out = delta_p(n, 0.5 * (e * in - vx * vx - vy * vy), va, vb);
+  dp_out = delta_p(n, temperature(e, in, vx, vy), va, vb);
 }
 
 // --------------------------------------------------------------------------
@@ -350,6 +364,36 @@ struct StageLds {
   Real fy[2 * G][BY + 1][64];
   // x advection of the first group, parked while the force is computed
   Real ga[G][BY][64];
+};
+
+// FP32 storage: the equilibrium's departure from w rho0 (collision
+// arithmetic, FP32 like the rest of it) from the FP64 moments, in per-axis
+// factors with w rho0 taken out exactly and every term small (nothing
+// cancels):
+//   cfe w_x w_y [dn0 (1 + hx)(1 + hy) + rho0 ((1 + hx)(1 + hy) - (1 + h0x)(1 + h0y))]
+//     = [cfe w_x (dn0 (1 + hx) + rho0 (hx - h0x))] [w_y (1 + hy)]
+//       + [cfe rho0 w_x (1 + h0x)] [w_y (hy - h0y)]
+// (cfe = B dt / tau, dn0 = n - rho0, h0 = 0 for tref = 1), so each population
+// takes two FMAs on top of its accumulator.
+struct Fp32Equilibrium {
+  float px[5], qx[5], by[5], hy_w[5];
+  __device__ __forceinline__ void set(const StageArgs& a, double sn, const double hx[5], const double hy[5]) {
+    const double cfe = (a.B * a.dt) * a.inv_tau;
+    const float cfef = (float)cfe, dn0f = (float)(sn - a.rho0), rho0f = (float)a.rho0;
+    const float crf = (float)(cfe * a.rho0);
+    // h0 = (theta / 2) He2 + (theta^2 / 8) He4 of the base, per index
+    const double c2 = 0.5 * (a.tref - 1.0), c4 = 0.5 * c2 * c2;
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+      const double h0 = fmadd(c4, HE.v[4][i], c2 * HE.v[2][i]);
+      const float w = (float)Wk[i];
+      const float hxi = (float)hx[i], dxi = (float)(hx[i] - h0), dyi = (float)(hy[i] - h0);
+      px[i] = (cfef * w) * __builtin_fmaf(dn0f, 1.0f + hxi, rho0f * dxi);
+      qx[i] = crf * (float)(Wk[i] * (1.0 + h0));
+      by[i] = __builtin_fmaf(w, (float)hy[i], w);
+      hy_w[i] = w * dyi;
+    }
+  }
 };
 
 // One 64 x BY tile (origin x0, y0) of one RK stage.
@@ -646,21 +690,21 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
 #pragma unroll
       for (int m = -3; m <= 3; ++m) {
         const int am = m < 0 ? -m : m;
-        if (GW[l][am] != 0.0) gxs += (l * GW[l][am]) * (mp[c + m * TW + l] - mp[c + m * TW - l]);
-        if (GL[l - 1][am] != 0.0) lxs += GL[l - 1][am] * (mn[c + m * TW + l] - mn[c + m * TW - l]);
+        if (GW[l][am] != 0.0) gxs = fmadd(l * GW[l][am], mp[c + m * TW + l] - mp[c + m * TW - l], gxs);
+        if (GL[l - 1][am] != 0.0) lxs = fmadd(GL[l - 1][am], mn[c + m * TW + l] - mn[c + m * TW - l], lxs);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int m = -3; m <= 3; ++m) {
         const int am = m < 0 ? -m : m;
-        if (GW[l][am] != 0.0) gys += (l * GW[l][am]) * (mp[c + l * TW + m] - mp[c - l * TW + m]);
-        if (GL[l - 1][am] != 0.0) lys += GL[l - 1][am] * (mn[c + l * TW + m] - mn[c - l * TW + m]);
+        if (GW[l][am] != 0.0) gys = fmadd(l * GW[l][am], mp[c + l * TW + m] - mp[c - l * TW + m], gys);
+        if (GL[l - 1][am] != 0.0) lys = fmadd(GL[l - 1][am], mn[c + l * TW + m] - mn[c - l * TW + m], lys);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
     const double inv_nc = 1.0 / mn[c];
-    Fx = gxs * a.inv_ds * inv_nc + a.sigma * (lxs * a.inv_ds3);
-    Fy = gys * a.inv_ds * inv_nc + a.sigma * (lys * a.inv_ds3);
+    Fx = fmadd(a.sigma, lxs * a.inv_ds3, (gxs * a.inv_ds) * inv_nc);
+    Fy = fmadd(a.sigma, lys * a.inv_ds3, (gys * a.inv_ds) * inv_nc);
   }
   // materialise the force here (left alone, the compiler interleaves the
   // stencils with the population stream and runs out of registers)
@@ -677,7 +721,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
   // populations (their moments) and is added at the end.
   const double Bdt = a.B * a.dt;
   const Real cx = (Real)(-Bdt * Fx), cy = (Real)(-Bdt * Fy);
-  const Real cb = (Real)(a.B * (1.0 - a.dt * a.inv_tau));
+  const Real cb = (Real)(a.B * fmadd(-a.dt, a.inv_tau, 1.0));
   const Real cadv = (Real)(-Bdt * a.inv_ds);
   const Real rA = (Real)a.A;
   Real acc[25];
@@ -696,7 +740,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
   auto local_terms = [&](int k, Real fk) {
     const int kx = k % 5, ky = k / 5;
     fsum.add(k, (double)fk);
-    acc[k] += tfac * fk;
+    acc[k] = fmadd(tfac, fk, acc[k]);
     // the force term acts on the whole population: with FP32 storage the
     // base rho0 b_kx b_ky (a uniform value, read through the scalar cache)
     // is added back for it
@@ -704,8 +748,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
     const Real tfx = cx * ff, tfy = cy * ff;
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
-      acc[5 * ky + i] += (Real)MT.v[i][kx] * tfx;
-      acc[5 * i + kx] += (Real)MT.v[i][ky] * tfy;
+      acc[5 * ky + i] = fmadd((Real)MT.v[i][kx], tfx, acc[5 * ky + i]);
+      acc[5 * i + kx] = fmadd((Real)MT.v[i][ky], tfy, acc[5 * i + kx]);
     }
   };
 
@@ -719,9 +763,9 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
       Real adv = advx[j];
       if (ky != 2) {
         const Real ryt = fy_sh[t % NB][ty + 1][tx];
-        adv += (Real)Rk[ky] * (ryt - ryl[j]);
+        adv = fmadd((Real)Rk[ky], ryt - ryl[j], adv);
       }
-      acc[k] += cadv * adv;
+      acc[k] = fmadd(cadv, adv, acc[k]);
     }
   };
 
@@ -777,51 +821,26 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
   double sn = fsum.n, se = fsum.e;
   if (F32) {
     sn += a.rho0;
-    se += 2.0 * a.rho0 * a.tref;
+    se = fmadd(2.0 * a.rho0, a.tref, se);
   }
   const double inv_n = 1.0 / sn;
   const double ux = fsum.jx * inv_n, uy = fsum.jy * inv_n;
-  const double T = 0.5 * (se * inv_n - ux * ux - uy * uy);
+  const double T = temperature(se, inv_n, ux, uy);
   double hx[5], hy[5];
   hfac(ux, T - 1.0, hx);
   hfac(uy, T - 1.0, hy);
   const double cfe = Bdt * a.inv_tau;
-  const double dn0 = sn - a.rho0;
-  // FP32 storage: the equilibrium's departure from w rho0 (collision
-  // arithmetic, FP32 like the rest of it) from the FP64 moments, in per-axis
-  // factors with w rho0 taken out exactly and every term small (nothing
-  // cancels):
-  //   cfe w_x w_y [dn0 (1 + hx)(1 + hy) + rho0 ((1 + hx)(1 + hy) - (1 + h0x)(1 + h0y))]
-  //     = [cfe w_x (dn0 (1 + hx) + rho0 (hx - h0x))] [w_y (1 + hy)]
-  //       + [cfe rho0 w_x (1 + h0x)] [w_y (hy - h0y)]
-  // (h0 = 0 for tref = 1), so each population takes two FMAs on top of its
-  // accumulator.
-  float px[5], qx[5], by[5], hy_w[5];
-  if (F32) {
-    const float cfef = (float)cfe, dn0f = (float)dn0, rho0f = (float)a.rho0;
-    const float crf = (float)(cfe * a.rho0);
-    // h0 = (theta / 2) He2 + (theta^2 / 8) He4 of the base, per index
-    const double c2 = 0.5 * (a.tref - 1.0), c4 = 0.5 * c2 * c2;
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      const double h0 = c2 * HE.v[2][i] + c4 * HE.v[4][i];
-      const float w = (float)Wk[i];
-      const float hxi = (float)hx[i], dxi = (float)(hx[i] - h0), dyi = (float)(hy[i] - h0);
-      px[i] = (cfef * w) * __builtin_fmaf(dn0f, 1.0f + hxi, rho0f * dxi);
-      qx[i] = crf * (float)(Wk[i] * (1.0 + h0));
-      by[i] = __builtin_fmaf(w, (float)hy[i], w);
-      hy_w[i] = w * dyi;
-    }
-  }
+  Fp32Equilibrium q;
+  if (F32) q.set(a, sn, hx, hy);
   MomSum dsum;
 #pragma unroll
   for (int k = 0; k < 25; ++k) {
     const int kx = k % 5, ky = k / 5;
     Real out;
     if (F32)
-      out = (Real)__builtin_fmaf(px[kx], by[ky], __builtin_fmaf(qx[kx], hy_w[ky], (float)acc[k]));
+      out = (Real)__builtin_fmaf(q.px[kx], q.by[ky], __builtin_fmaf(q.qx[kx], q.hy_w[ky], (float)acc[k]));
     else
-      out = acc[k] + (Real)(cfe * (sn * (Wk[kx] * (1.0 + hx[kx])) * (Wk[ky] * (1.0 + hy[ky]))));
+      out = (Real)fmadd(cfe, (sn * (Wk[kx] * (1.0 + hx[kx]))) * (Wk[ky] * (1.0 + hy[ky])), (double)acc[k]);
     if (active) {
       if constexpr (XSPEC) dst[k * ps + own] = out;
       else bstore<Real>(out, plane_rsrc(a.fdst, k, pbytes, rbytes), ownb);
@@ -855,23 +874,8 @@ __device__ __forceinline__ int find_instance(const InstDesc* inst, int ninst, in
   return lo;
 }
 
-// Stage kernel: one launch over the tile queue of every instance of a batch,
-// one tile per workgroup.  Consecutive workgroups are dispatched to different
-// XCDs, so workgroup b takes tile (b mod 8) * ceil(T/8) + b / 8 (each XCD
-// works through a contiguous run of the queue).  Within an instance tiles are
-// numbered row by row inside strips of ba.strip tile columns (whole rows when
-// 0): an XCD then runs vertically adjacent tiles close together in time, so
-// the halo rows they share are still in its L2 (in row order a tile's lower
-// neighbour starts about half a tile lifetime later and misses them).
-template <typename Real, int BY, bool WALLS, bool FN, bool XSPEC>
-__global__ void __launch_bounds__(64 * BY, min_waves_per_simd<Real>()) stage_kernel(const BatchArgs ba) {
-  __shared__ StageLds<Real, BY, wide_lds<Real, BY, XSPEC>()> sm;
-  const int bid = blockIdx.x;
-  const int q8 = ba.total_tiles >> 3, r8 = ba.total_tiles & 7, xcd = bid & 7;
-  const int t = xcd * q8 + (xcd < r8 ? xcd : r8) + (bid >> 3);
-  // the instance index is uniform: keep it (and so the descriptor loads) scalar
-  const int i = __builtin_amdgcn_readfirstlane(find_instance(ba.inst, ba.ninst, t));
-  const InstDesc& d = ba.inst[i];
+// One stage of instance d.
+__device__ __forceinline__ StageArgs stage_args(const BatchArgs& ba, const InstDesc& d) {
   StageArgs a;
   a.g = d.g;
   a.fsrc = d.f[ba.stage];
@@ -893,6 +897,27 @@ __global__ void __launch_bounds__(64 * BY, min_waves_per_simd<Real>()) stage_ker
   a.tref = d.tref;
   a.base = d.base;
   a.wguard = ba.wguard;
+  return a;
+}
+
+// Stage kernel: one launch over the tile queue of every instance of a batch,
+// one tile per workgroup.  Consecutive workgroups are dispatched to different
+// XCDs, so workgroup b takes tile (b mod 8) * ceil(T/8) + b / 8 (each XCD
+// works through a contiguous run of the queue).  Within an instance tiles are
+// numbered row by row inside strips of ba.strip tile columns (whole rows when
+// 0): an XCD then runs vertically adjacent tiles close together in time, so
+// the halo rows they share are still in its L2 (in row order a tile's lower
+// neighbour starts about half a tile lifetime later and misses them).
+template <typename Real, int BY, bool WALLS, bool FN, bool XSPEC>
+__global__ void __launch_bounds__(64 * BY, min_waves_per_simd<Real>()) stage_kernel(const BatchArgs ba) {
+  __shared__ StageLds<Real, BY, wide_lds<Real, BY, XSPEC>()> sm;
+  const int bid = blockIdx.x;
+  const int q8 = ba.total_tiles >> 3, r8 = ba.total_tiles & 7, xcd = bid & 7;
+  const int t = xcd * q8 + (xcd < r8 ? xcd : r8) + (bid >> 3);
+  // the instance index is uniform: keep it (and so the descriptor loads) scalar
+  const int i = __builtin_amdgcn_readfirstlane(find_instance(ba.inst, ba.ninst, t));
+  const InstDesc& d = ba.inst[i];
+  const StageArgs a = stage_args(ba, d);
   const int local = t - d.tile_base;
   int tile_x, tile_y;
   if (ba.strip > 0 && ba.strip < d.tiles_x) {
@@ -915,6 +940,15 @@ __global__ void __launch_bounds__(64 * BY, min_waves_per_simd<Real>()) stage_ker
 // --------------------------------------------------------------------------
 // diffuse-reflection ghosts (Sec. 3.4.2, walls across y)
 // --------------------------------------------------------------------------
+
+// Quadratic extrapolation through a wall from the three interior rows next to
+// it (v0 adjacent): the ghost rows e1, e2, e3, nearest first.
+template <typename Real>
+__device__ __forceinline__ void wall_extrapolate(Real v0, Real v1, Real v2, Real& e1, Real& e2, Real& e3) {
+  e1 = fmadd((Real)3, v0 - v1, v2);
+  e2 = fmadd((Real)6, v0, fmadd((Real)-8, v1, (Real)3 * v2));
+  e3 = fmadd((Real)10, v0, fmadd((Real)-15, v1, (Real)6 * v2));
+}
 
 template <typename Real>
 __global__ void walls_kernel(const WallBatchArgs wa) {
@@ -976,9 +1010,8 @@ __global__ void walls_kernel(const WallBatchArgs wa) {
       const int k = 5 * ky + kx;
       Real* pk = f + k * ps + x;
       const Real v0 = pk[r0 * rs], v1 = pk[r1 * rs], v2 = pk[r2 * rs];
-      const Real e1 = (Real)3 * v0 - (Real)3 * v1 + v2;
-      const Real e2 = (Real)6 * v0 - (Real)8 * v1 + (Real)3 * v2;
-      const Real e3 = (Real)10 * v0 - (Real)15 * v1 + (Real)6 * v2;
+      Real e1, e2, e3;
+      wall_extrapolate(v0, v1, v2, e1, e2, e3);
       pk[g1 * rs] = e1;
       pk[g2 * rs] = e2;
       pk[g3 * rs] = e3;
@@ -986,8 +1019,8 @@ __global__ void walls_kernel(const WallBatchArgs wa) {
         // face between the adjacent interior row and the first ghost row;
         // upwind order (far interior ... ghost) is the same at both walls
         double rec = (double)weno_rec(v2, v1, v0, e1, e2);
-        if (F32) rec += bw[kx] * bw[ky] * rho0;
-        out += Rk[ky] * rec;
+        if (F32) rec = fmadd(bw[kx] * bw[ky], rho0, rec);
+        out = fmadd(Rk[ky], rec, out);
       }
     }
   }
@@ -1000,7 +1033,7 @@ __global__ void walls_kernel(const WallBatchArgs wa) {
 #pragma unroll
   for (int ky = 0; ky < 5; ++ky) {
     const bool emitted = wall ? (ky < 2) : (ky > 2);
-    if (emitted) den += Wk[ky] * (1.0 + hy[ky]) * Rk[ky];
+    if (emitted) den = fmadd(Wk[ky] * (1.0 + hy[ky]), Rk[ky], den);
   }
   const double nw = -out / den;
   d.nw[wall * nx + x] = nw;
@@ -1011,8 +1044,8 @@ __global__ void walls_kernel(const WallBatchArgs wa) {
 #pragma unroll
     for (int kx = 0; kx < 5; ++kx) {
       const int k = 5 * ky + kx;
-      double v = nw * (Wk[kx] * (1.0 + hx[kx])) * (Wk[ky] * (1.0 + hy[ky]));
-      if (F32) v -= bw[kx] * bw[ky] * rho0;
+      double v = (nw * (Wk[kx] * (1.0 + hx[kx]))) * (Wk[ky] * (1.0 + hy[ky]));
+      if (F32) v = fmadd(-(bw[kx] * bw[ky]), rho0, v);
       Real* pk = f + k * ps + x;
       pk[g1 * rs] = (Real)v;
       pk[g2 * rs] = (Real)v;
@@ -1020,6 +1053,12 @@ __global__ void walls_kernel(const WallBatchArgs wa) {
     }
   }
 }
+
+}  // namespace olbk
+
+#include "olb_split.hpp"
+
+namespace olbk {
 
 // --------------------------------------------------------------------------
 // set-up and read-out
@@ -1066,7 +1105,7 @@ __global__ void moments_kernel(Geometry g, const Real* __restrict__ f, double* _
   out[m] = n;
   out[N + m] = ux;
   out[2 * N + m] = uy;
-  out[3 * N + m] = 0.5 * (e * in - ux * ux - uy * uy);
+  out[3 * N + m] = temperature(e, in, ux, uy);
 }
 
 template <typename Real>
@@ -1097,7 +1136,7 @@ __global__ void pack_kernel(Geometry g, const Real* __restrict__ f, double* __re
   for (int k = 0; k < 25; ++k) {
     double v = (double)f[k * g.ps + own];
     if (std::is_same<Real, float>::value)
-      v += (Wk[k % 5] * (1.0 + h0[k % 5])) * (Wk[k / 5] * (1.0 + h0[k / 5])) * rho0;
+      v = fmadd((Wk[k % 5] * (1.0 + h0[k % 5])) * (Wk[k / 5] * (1.0 + h0[k / 5])), rho0, v);
     out[k * N + m] = v;
   }
 }
@@ -1115,7 +1154,7 @@ __global__ void unpack_kernel(Geometry g, const double* __restrict__ in, Real* _
   for (int k = 0; k < 25; ++k) {
     double v = in[k * N + m];
     if (std::is_same<Real, float>::value)
-      v -= (Wk[k % 5] * (1.0 + h0[k % 5])) * (Wk[k / 5] * (1.0 + h0[k / 5])) * rho0;
+      v = fmadd(-((Wk[k % 5] * (1.0 + h0[k % 5])) * (Wk[k / 5] * (1.0 + h0[k / 5]))), rho0, v);
     f[k * g.ps + own] = (Real)v;
   }
 }
@@ -1156,6 +1195,29 @@ hipError_t launch_stage(const BatchArgs& a, int real_bytes, int by, bool walls, 
     if (by == 8) return stage_x<float, 8>(a, walls, xspec, grid, s);
   }
   return hipErrorInvalidValue;
+}
+
+template <typename Real, bool WALLS>
+static hipError_t split_by(const BatchArgs& a, bool xspec, int grid, hipStream_t s) {
+  const dim3 block(SPLIT_THREADS);
+  const bool fn = a.A != 0.0;
+  if (xspec && fn)
+    hipLaunchKernelGGL((split_stage_kernel<Real, WALLS, true, true>), dim3(grid), block, 0, s, a);
+  else if (xspec)
+    hipLaunchKernelGGL((split_stage_kernel<Real, WALLS, false, true>), dim3(grid), block, 0, s, a);
+  else if (fn)
+    hipLaunchKernelGGL((split_stage_kernel<Real, WALLS, true, false>), dim3(grid), block, 0, s, a);
+  else
+    hipLaunchKernelGGL((split_stage_kernel<Real, WALLS, false, false>), dim3(grid), block, 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_split(const BatchArgs& a, int real_bytes, bool walls, bool xspec, hipStream_t s) {
+  const int grid = a.total_tiles;
+  if (grid < 1) return hipErrorInvalidValue;
+  if (real_bytes == 8)
+    return walls ? split_by<double, true>(a, xspec, grid, s) : split_by<double, false>(a, xspec, grid, s);
+  return walls ? split_by<float, true>(a, xspec, grid, s) : split_by<float, false>(a, xspec, grid, s);
 }
 
 hipError_t launch_walls(const WallBatchArgs& a, int real_bytes, int wall_blocks, hipStream_t s) {

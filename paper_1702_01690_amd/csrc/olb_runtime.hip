@@ -13,6 +13,7 @@
 // context (olb_ctx) is an engine with one instance; olb_batch exposes N.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -119,6 +120,8 @@ struct Engine {
   bool walls = false;
   bool xspec = false;              // specular planes at both ends of x
   int by = 8;
+  bool by_set = false;             // the caller chose the tile height: the stage kernel at that height
+  bool split = false;              // every stage by the split kernel (upload_desc)
   int strip = 8;                   // tile order (BatchArgs::strip)
   int cur = 0;                     // carry index of the current f^n
   int total_tiles = 0, wall_blocks = 0;
@@ -155,13 +158,37 @@ struct Engine {
     for (int k = 0; k < 25; ++k) d.base[k] = (float)(d.rho0 * bw[k % 5] * bw[k / 5]);
   }
 
+  static int64_t tile_count(const olb_params& q, int tx, int ty) {
+    return (int64_t)((q.nx + tx - 1) / tx) * ((q.ny + ty - 1) / ty);
+  }
+
+  // Which kernel takes the stages, unless the caller chose a tile height: the
+  // split kernel while the stage kernel's tiles leave it the slower one.  A
+  // stage kernel tile costs the chip about three split tiles (FP64: 1024^2
+  // takes 8192 split tiles 220 us, 2176 stage tiles 175 us; FP32: 143 and
+  // 97 us), but a launch of it takes 21 us (FP32 17) however few tiles it has,
+  // about 800 split tiles' time, where a launch of the split kernel takes 9.
+  // Walls cost the stage kernel a launch of their own (8 us and more), and its
+  // specular-x variants run one workgroup per CU instead of two.
+  bool split_is_faster() const {
+    int64_t ts = 0, tq = 0;
+    for (const auto& q : p) {
+      ts += tile_count(q, olbk::SPLIT_X, olbk::SPLIT_Y);
+      tq += tile_count(q, olbk::TILE_X, 8);
+    }
+    const double per_tile = (rb == 8 ? 3.0 : 2.5) * (xspec ? 1.5 : 1.0);
+    return (double)ts <= std::max(800.0, per_tile * (double)tq) + (walls ? 300.0 : 0.0);
+  }
+
   // tile counts for the current block height, and the device table
   olb_status upload_desc() {
     int tiles = 0, blocks = 0;
+    split = !by_set && split_is_faster();
+    const int tx = split ? olbk::SPLIT_X : olbk::TILE_X, ty = split ? olbk::SPLIT_Y : by;
     for (int i = 0; i < count(); ++i) {
       olbk::InstDesc& d = desc[i];
-      d.tiles_x = (p[i].nx + olbk::TILE_X - 1) / olbk::TILE_X;
-      d.tiles_y = (p[i].ny + by - 1) / by;
+      d.tiles_x = (p[i].nx + tx - 1) / tx;
+      d.tiles_y = (p[i].ny + ty - 1) / ty;
       d.tile_base = tiles;
       d.wall_block_base = blocks;
       tiles += d.tiles_x * d.tiles_y;
@@ -423,7 +450,7 @@ struct Engine {
   // stage launch over every instance's tiles
   olb_status enqueue_step() {
     for (int s = 0; s < 3; ++s) {
-      if (walls) {
+      if (walls && !split) {
         olbk::WallBatchArgs wa{d_desc, count(), s};
         olb_status e = hip(olbk::launch_walls(wa, rb, wall_blocks, stream), "wall kernel");
         if (e) return e;
@@ -439,7 +466,8 @@ struct Engine {
       ba.A = olbc::RK_A[s];
       ba.B = olbc::RK_B[s];
       ba.wguard = 0x1p-1000;
-      olb_status e = hip(olbk::launch_stage(ba, rb, by, walls, xspec, stream), "stage kernel");
+      olb_status e = hip(split ? olbk::launch_split(ba, rb, walls, xspec, stream)
+                               : olbk::launch_stage(ba, rb, by, walls, xspec, stream), "stage kernel");
       if (e) return e;
       cur ^= 1;
     }
@@ -491,11 +519,26 @@ struct Engine {
     return OLB_OK;
   }
 
-  olb_status set_tile(int32_t b) {
+  olb_status choose_tile(int32_t b) {
+    olb_status s = check_tile(b);
+    if (s) return s;
+    if (by_set && b == by) return OLB_OK;
+    by_set = true;
+    by = b;
+    return upload_desc();
+  }
+
+  olb_status check_tile(int32_t b) {
     // 12 only with FP32 storage: two 12-wave workgroups per CU fit its
     // 80-register budget, while FP64 (128 registers) would run one
     if (b != 8 && b != 16 && !(b == 12 && rb == 4))
       return fail(OLB_E_ARG, "tile height must be 8 or 16 (or 12 with FP32 storage)");
+    return OLB_OK;
+  }
+
+  olb_status set_tile(int32_t b) {
+    olb_status s = check_tile(b);
+    if (s) return s;
     if (b == by) return OLB_OK;
     by = b;
     return upload_desc();
@@ -822,7 +865,7 @@ olb_status olb_set_f(olb_ctx* c, const double* f) { return c ? c->e.set_f(0, f) 
 olb_status olb_wall_density(olb_ctx* c, double* lo, double* hi) {
   return c ? c->e.wall_density(0, lo, hi) : OLB_E_ARG;
 }
-olb_status olb_set_tile(olb_ctx* c, int32_t by) { return c ? c->e.set_tile(by) : OLB_E_ARG; }
+olb_status olb_set_tile(olb_ctx* c, int32_t by) { return c ? c->e.choose_tile(by) : OLB_E_ARG; }
 olb_status olb_set_base_temperature(olb_ctx* c, double T) { return c ? c->e.set_base_temperature(0, T) : OLB_E_ARG; }
 olb_status olb_set_tile_order(olb_ctx* c, int32_t strip) { return c ? c->e.set_tile_order(strip) : OLB_E_ARG; }
 olb_status olb_launch_counts(const olb_ctx* c, int32_t* stage, int32_t* walls) {
@@ -892,7 +935,7 @@ olb_status olb_batch_use_graph(olb_batch* b, int32_t steps_per_graph) {
   b->e.graph_steps = steps_per_graph == 0 ? 0 : 2 * ((steps_per_graph + 1) / 2);
   return OLB_OK;
 }
-olb_status olb_batch_set_tile(olb_batch* b, int32_t by) { return b ? b->e.set_tile(by) : OLB_E_ARG; }
+olb_status olb_batch_set_tile(olb_batch* b, int32_t by) { return b ? b->e.choose_tile(by) : OLB_E_ARG; }
 olb_status olb_batch_set_base_temperature(olb_batch* b, int32_t i, double T) {
   return b ? b->e.set_base_temperature(i, T) : OLB_E_ARG;
 }

@@ -19,6 +19,10 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", "-shared", f"--offload-arch={ARCH}",
          # are indexed by population); the default size limit left the FP32
          # specular-x instantiations rolled, with the accumulators in scratch
          "-mllvm", "-pragma-unroll-threshold=100000",
+         # the resident kernel's loop over stages: left on, this pass moves the
+         # FP64 constants of its body (one scalar move each where they are used)
+         # out of the loop, into more scalar registers than there are
+         "-mllvm", "-disable-machine-licm",
          "-Wall", "-Wno-unused-function",
          "-I", os.path.join(ROOT, "include")]
 

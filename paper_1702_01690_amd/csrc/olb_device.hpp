@@ -78,11 +78,18 @@ struct WallBatchArgs {
 constexpr int TILE_X = 63;
 // Tiles of the split stage kernel (olb_split.hpp).
 constexpr int SPLIT_X = 16, SPLIT_Y = 8;
+// Lattices that a workgroup of the resident kernel holds whole: up to 64 NG
+// nodes, and up to resident_places(NG) with three ghost rows at each wall.
+constexpr int RESIDENT_GROUPS = 3;
+constexpr int resident_places(int ng) { return 64 * ng + 16; }
 
 // One workgroup per tile of the batch's tile queue.
 hipError_t launch_stage(const BatchArgs& a, int real_bytes, int by, bool walls, bool xspec, hipStream_t s);
 // The same with 16 x 8 tiles, wall ghosts included (no launch_walls).
 hipError_t launch_split(const BatchArgs& a, int real_bytes, bool walls, bool xspec, hipStream_t s);
+// nsteps whole RK-3 steps of every instance, each in one workgroup (every
+// lattice fits ng; a.stage, a.A, a.B and the tiles are unused).
+hipError_t launch_resident(const BatchArgs& a, int nsteps, int ng, int real_bytes, bool walls, hipStream_t s);
 // wall_blocks: sum over instances of ceil(nx / 64).
 hipError_t launch_walls(const WallBatchArgs& a, int real_bytes, int wall_blocks, hipStream_t s);
 // f = f^eq(n, u, T) from device fields [4][ny][nx]; also writes the carry.

@@ -1220,6 +1220,30 @@ hipError_t launch_split(const BatchArgs& a, int real_bytes, bool walls, bool xsp
   return walls ? split_by<float, true>(a, xspec, grid, s) : split_by<float, false>(a, xspec, grid, s);
 }
 
+template <typename Real, int NG>
+static hipError_t resident_by(const BatchArgs& a, int nsteps, bool walls, hipStream_t s) {
+  const dim3 grid(a.ninst), block(Resident<NG>::THREADS);
+  if (walls)
+    hipLaunchKernelGGL((resident_kernel<Real, NG, true>), grid, block, 0, s, a, nsteps);
+  else
+    hipLaunchKernelGGL((resident_kernel<Real, NG, false>), grid, block, 0, s, a, nsteps);
+  return hipGetLastError();
+}
+
+hipError_t launch_resident(const BatchArgs& a, int nsteps, int ng, int real_bytes, bool walls, hipStream_t s) {
+  if (a.ninst < 1 || nsteps < 1) return hipErrorInvalidValue;
+  if (real_bytes == 8) {
+    if (ng == 1) return resident_by<double, 1>(a, nsteps, walls, s);
+    if (ng == 2) return resident_by<double, 2>(a, nsteps, walls, s);
+    if (ng == 3) return resident_by<double, 3>(a, nsteps, walls, s);
+  } else {
+    if (ng == 1) return resident_by<float, 1>(a, nsteps, walls, s);
+    if (ng == 2) return resident_by<float, 2>(a, nsteps, walls, s);
+    if (ng == 3) return resident_by<float, 3>(a, nsteps, walls, s);
+  }
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_walls(const WallBatchArgs& a, int real_bytes, int wall_blocks, hipStream_t s) {
   dim3 block(64), grid(wall_blocks, 2);
   if (real_bytes == 8)

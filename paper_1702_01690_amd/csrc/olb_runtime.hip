@@ -122,6 +122,7 @@ struct Engine {
   int by = 8;
   bool by_set = false;             // the caller chose the tile height: the stage kernel at that height
   bool split = false;              // every stage by the split kernel (upload_desc)
+  int resident = 0;                // whole steps by the resident kernel, its NG (upload_desc)
   int strip = 8;                   // tile order (BatchArgs::strip)
   int cur = 0;                     // carry index of the current f^n
   int total_tiles = 0, wall_blocks = 0;
@@ -180,10 +181,23 @@ struct Engine {
     return (double)ts <= std::max(800.0, per_tile * (double)tq) + (walls ? 300.0 : 0.0);
   }
 
+  // NG of the resident kernel that holds every instance whole, or 0
+  int resident_groups() const {
+    if (xspec) return 0;
+    int ng = 1;
+    for (const auto& q : p) {
+      const int64_t nodes = (int64_t)q.nx * q.ny, places = nodes + (walls ? 6 * (int64_t)q.nx : 0);
+      while (ng <= olbk::RESIDENT_GROUPS && (nodes > 64 * ng || places > olbk::resident_places(ng))) ++ng;
+      if (ng > olbk::RESIDENT_GROUPS) return 0;
+    }
+    return ng;
+  }
+
   // tile counts for the current block height, and the device table
   olb_status upload_desc() {
     int tiles = 0, blocks = 0;
-    split = !by_set && split_is_faster();
+    resident = by_set ? 0 : resident_groups();
+    split = !by_set && !resident && split_is_faster();
     const int tx = split ? olbk::SPLIT_X : olbk::TILE_X, ty = split ? olbk::SPLIT_Y : by;
     for (int i = 0; i < count(); ++i) {
       olbk::InstDesc& d = desc[i];
@@ -446,6 +460,31 @@ struct Engine {
     return hip(hipStreamSynchronize(stream), "stream sync");
   }
 
+  // RK-3 steps; the resident kernel takes up to 256 in a launch (a fraction of
+  // a millisecond; more in one launch would gain less than a percent)
+  olb_status enqueue_steps(int32_t n) {
+    while (n > 0) {
+      const int32_t k = resident ? std::min<int32_t>(n, 256) : 1;
+      olb_status s = resident ? enqueue_resident(k) : enqueue_step();
+      if (s) return s;
+      n -= k;
+    }
+    return OLB_OK;
+  }
+
+  olb_status enqueue_resident(int32_t n) {
+    olbk::BatchArgs ba{};
+    ba.inst = d_desc;
+    ba.ninst = count();
+    ba.cur = cur;
+    ba.flag = flag;
+    ba.wguard = 0x1p-1000;
+    olb_status e = hip(olbk::launch_resident(ba, n, resident, rb, walls, stream), "resident kernel");
+    if (e) return e;
+    cur ^= n & 1;
+    return OLB_OK;
+  }
+
   // one RK-3 step: per stage, wall ghosts of f_src (with walls), then the
   // stage launch over every instance's tiles
   olb_status enqueue_step() {
@@ -484,15 +523,13 @@ struct Engine {
       if (!graph_exec) {
         olb_status s = hip(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal), "graph capture");
         if (s) return fail(OLB_E_STATE, err + " (graphs need a non-default stream)");
-        for (int k = 0; k < graph_steps; ++k) {
-          s = enqueue_step();
-          if (s) {
-            hipGraph_t g = nullptr;
-            (void)hipStreamEndCapture(stream, &g);
-            if (g) (void)hipGraphDestroy(g);
-            cur = 0;
-            return s;
-          }
+        s = enqueue_steps(graph_steps);
+        if (s) {
+          hipGraph_t g = nullptr;
+          (void)hipStreamEndCapture(stream, &g);
+          if (g) (void)hipGraphDestroy(g);
+          cur = 0;
+          return s;
         }
         s = hip(hipStreamEndCapture(stream, &graph), "graph capture end");
         if (s) return s;
@@ -504,11 +541,7 @@ struct Engine {
       if (s) return s;
       left -= graph_steps;
     }
-    for (int32_t k = 0; k < left; ++k) {
-      olb_status s = enqueue_step();
-      if (s) return s;
-    }
-    return OLB_OK;
+    return enqueue_steps(left);
   }
 
   olb_status set_tile_order(int32_t w) {

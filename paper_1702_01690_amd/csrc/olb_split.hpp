@@ -4,9 +4,9 @@
 //
 // The stage kernel streams the 25 populations through one workgroup, a barrier
 // each: about 20 us from the first load to the last store, whatever the
-// lattice (FP64 32 x 32: 20.9 us a stage; the split kernel takes 9.2 us, of
+// lattice (FP64 32 x 32: 20.9 us a stage; the split kernel takes 8.4 us, of
 // which the loads of a tile are a third and the face reconstructions another;
-// with walls 28 against 10.6 us, in a box 31 against 10.6 us).  Here five groups of waves take the five velocity rows (ky) of a
+// with walls 28 against 10 us, in a box 31 against 10 us).  Here five groups of waves take the five velocity rows (ky) of a
 // tile at the same time, with every population of the tile in LDS: a thread
 // owns one node and the populations (0..4, ky), reconstructs their left and
 // lower faces, and gathers their force term from the node's 25 values.  The
@@ -113,14 +113,15 @@ __device__ __forceinline__ Real face_value(const StageArgs& a, const Real (&c)[6
   return positive ? face_value(a, c[0], c[1], c[2], c[3], c[4]) : face_value(a, c[5], c[4], c[3], c[2], c[1]);
 }
 
-// M and |p_y| by row, for kernels whose velocity row is a (uniform) value
+// M, p_y and |p_y| by row, for kernels whose velocity row is a (uniform) value
 struct RowTables {
-  double m[5][5], speed[5];
+  double m[5][5], p[5], speed[5];
 };
 constexpr RowTables make_row_tables() {
   RowTables t{};
   for (int k = 0; k < 5; ++k) {
     for (int j = 0; j < 5; ++j) t.m[k][j] = MT.v[k][j];
+    t.p[k] = Rk[k];
     t.speed[k] = Rk[k] < 0.0 ? -Rk[k] : Rk[k];
   }
   return t;
@@ -131,9 +132,8 @@ __constant__ const RowTables row_tables = make_row_tables();
 // in acc on entry; own and force terms and advection are added source by
 // source in population order, as the stage kernel adds them.  f(ky, kx) is the
 // node's value of a population, adv[kx] the advection difference of (kx, row).
-// The row is a uniform value, not a template argument: a launch on a small
-// lattice runs its code once, from a cold instruction cache, and five copies
-// of it cost more than the loops.
+// The row is a uniform value rather than a template argument, which would
+// multiply the code of the faces by five and runs no faster.
 template <typename Real, typename F>
 __device__ __forceinline__ void row_terms(const StageArgs& a, int row, double Fx, double Fy, Real acc[5],
                                           const Real adv[5], F f) {
@@ -145,15 +145,17 @@ __device__ __forceinline__ void row_terms(const StageArgs& a, int row, double Fx
   const Real tfac = (Real)(a.B * fmadd(-a.dt, a.inv_tau, 1.0));
   const Real cadv = (Real)(-Bdt * a.inv_ds);
   // the five values of the next source row are read while one is added
-  Real cur[5], next[5];
+  Real mrow[5], cur[5], next[5];
 #pragma unroll
-  for (int kx = 0; kx < 5; ++kx) cur[kx] = f(0, kx);
-#pragma unroll 1
+  for (int kx = 0; kx < 5; ++kx) {
+    mrow[kx] = (Real)row_tables.m[row][kx];
+    cur[kx] = f(0, kx);
+  }
+#pragma unroll
   for (int ky = 0; ky < 5; ++ky) {
-    const int kn = ky < 4 ? ky + 1 : 4;
 #pragma unroll
-    for (int kx = 0; kx < 5; ++kx) next[kx] = f(kn, kx);
-    const Real m = (Real)row_tables.m[row][ky];
+    for (int kx = 0; kx < 5; ++kx) next[kx] = f(ky < 4 ? ky + 1 : 4, kx);
+    const Real m = mrow[ky];
     Real ff[5], tfy[5];
 #pragma unroll
     for (int kx = 0; kx < 5; ++kx) {
@@ -179,6 +181,7 @@ __device__ __forceinline__ void row_terms(const StageArgs& a, int row, double Fx
     }
 #pragma unroll
     for (int kx = 0; kx < 5; ++kx) cur[kx] = next[kx];
+    keep_order(acc[0], acc[1], acc[2], acc[3], acc[4]);
   }
 }
 
@@ -237,18 +240,20 @@ __device__ __forceinline__ void wall_pass1(const InstDesc& d, const WallSide& w,
 template <typename Real>
 struct WallEmission {
   static constexpr bool F32 = std::is_same<Real, float>::value;
-  double bw[5], hx[5], hy[5], den;
-  __device__ __forceinline__ WallEmission(const InstDesc& d, int high) {
-    double h0[5];
+  double bw[5], wx[5], wy[5], den;   // base factors, w (1 + h) of the wall state per axis
+  __device__ __forceinline__ void set(const InstDesc& d, int high) {
+    double h0[5], hx[5], hy[5];
     base_h0(d.tref, h0);
-#pragma unroll
-    for (int i = 0; i < 5; ++i) bw[i] = Wk[i] * (1.0 + h0[i]);
     hfac(d.uw[high], d.tw[high] - 1.0, hx);
     hfac(0.0, d.tw[high] - 1.0, hy);
     den = 0.0;
 #pragma unroll
-    for (int ky = 0; ky < 5; ++ky)
-      if (high ? ky < 2 : ky > 2) den = fmadd(Wk[ky] * (1.0 + hy[ky]), Rk[ky], den);
+    for (int i = 0; i < 5; ++i) {
+      bw[i] = Wk[i] * (1.0 + h0[i]);
+      wx[i] = Wk[i] * (1.0 + hx[i]);
+      wy[i] = Wk[i] * (1.0 + hy[i]);
+      if (high ? i < 2 : i > 2) den = fmadd(wy[i], Rk[i], den);
+    }
   }
   template <typename Recs>
   __device__ __forceinline__ double density(const InstDesc& d, int high, Recs recs) const {
@@ -266,11 +271,9 @@ struct WallEmission {
   }
   // emitted population (kx, 3 + j) at the low end, (kx, j) at the high end
   __device__ __forceinline__ Real value(const InstDesc& d, int high, double nw, int kx, int j) const {
-    auto pick = [&](double lo0, double lo1, double hi0, double hi1) { return high ? (j ? hi1 : hi0) : (j ? lo1 : lo0); };
-    const double hyk = pick(hy[3], hy[4], hy[0], hy[1]), by = pick(bw[3], bw[4], bw[0], bw[1]),
-                 wy = pick(Wk[3], Wk[4], Wk[0], Wk[1]);
-    double v = (nw * (Wk[kx] * (1.0 + hx[kx]))) * (wy * (1.0 + hyk));
-    if (F32) v = fmadd(-(bw[kx] * by), d.rho0, v);
+    auto pick = [&](const double* v) { return high ? (j ? v[1] : v[0]) : (j ? v[4] : v[3]); };
+    double v = (nw * wx[kx]) * pick(wy);
+    if (F32) v = fmadd(-(bw[kx] * pick(bw)), d.rho0, v);
     return (Real)v;
   }
 };
@@ -304,7 +307,10 @@ struct SplitLds {
   double F[2][SPLIT_NODES];
   union {
     Real eq[eq_slots<Real>()][SPLIT_NODES];
-    double rec[2][10][SPW];      // wall-face values, before the equilibrium
+    struct {                     // at a wall, before the equilibrium
+      double rec[2][10][SPW];    // wall-face values
+      WallEmission<Real> em[2];
+    };
   };
 };
 
@@ -548,6 +554,7 @@ __global__ void __launch_bounds__(SPLIT_THREADS, 6) split_stage_kernel(const Bat
                       {top, top + 1 < SPH ? top + 1 : -1, top + 2 < SPH ? top + 2 : -1}};
     };
     auto has = [&](int s) { return s == 0 ? y0 == 0 : top < SPH; };
+    if (tid >= SPLIT_THREADS - 2) sm.em[tid & 1].set(d, tid & 1);
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       if (has(s) && tid < 25 * SPW) {
@@ -570,7 +577,7 @@ __global__ void __launch_bounds__(SPLIT_THREADS, 6) split_stage_kernel(const Bat
         const WallSide w = side(s);
         double nw = 0.0;
         if (!mirror) {
-          const WallEmission<Real> em(d, s);
+          const WallEmission<Real>& em = sm.em[s];
           nw = em.density(d, s, [&](int jj, int kx) { return sm.rec[s][5 * jj + (fl ? 4 - kx : kx)][c]; });
 #pragma unroll
           for (int kx = 0; kx < 5; ++kx) {
@@ -593,6 +600,236 @@ __global__ void __launch_bounds__(SPLIT_THREADS, 6) split_stage_kernel(const Bat
     split_rows<Real, FN>(a, sm, ky, fn, lane, ownb, pbytes, rbytes);
   else
     split_moments<Real>(a, sm, lane, active, (int64_t)y * nx + x, N);
+}
+
+// --------------------------------------------------------------------------
+// whole steps of lattices that fit one workgroup
+// --------------------------------------------------------------------------
+
+// A workgroup per instance runs `nsteps` RK-3 steps with f in LDS throughout
+// (f^n in registers): a stage costs no launch and no trip to memory.  Lattices
+// of up to 64 NG nodes, periodic or with walls across y, periodic in x (the
+// rows of waves and half-channel columns of the one-dimensional tests).  The
+// bound is the chain of one stage: sums and carry, force, terms, four barriers
+// (six with walls), with the faces beside them; the sums and the force are
+// taken by waves of their own where 1024 threads allow it (NG < 3), by row 2's
+// otherwise.
+// Measured (FP64): 13 half channels of 1 x 160 nodes 44 -> 6.5 us a stage, of
+// which the faces are a third, the terms a fifth and the wall ghosts a sixth;
+// 315 waves of 20 .. 60 nodes 33 -> 3.1 us.
+// Directions one node wide have no advection and no force (every difference
+// along them is exactly zero) and are skipped.
+// Node i = y nx + x is at LDS place i, after three ghost rows with walls.
+template <int NG>
+struct Resident {
+  static constexpr int NODES = 64 * NG;
+  static constexpr int PLACES = resident_places(NG);   // stride of a plane, ghost rows included
+  static constexpr int GROUPS = NG < 3 ? 7 : 5;
+  static constexpr int THREADS = NODES * GROUPS;
+  static constexpr int COLS = PLACES / 9;              // widest walled lattice: (3 + 6) rows
+};
+
+template <typename Real, int NG>
+struct ResidentLds {
+  using R = Resident<NG>;
+  Real f[25][R::PLACES];
+  Real xf[20][R::PLACES], yf[20][R::PLACES];   // left and lower faces, by moving row / column
+  double cm[2][R::NODES];
+  double F[2][R::NODES];
+  Real eq[eq_slots<Real>()][R::NODES];
+  double rec[2][10][R::COLS];
+  WallEmission<Real> em[2];
+  int cc[7][R::NODES], cr[7][R::NODES];        // neighbours in the carried fields
+};
+
+template <typename Real, int NG, bool WALLS>
+__global__ void __launch_bounds__(Resident<NG>::THREADS, 4) resident_kernel(const BatchArgs ba, int nsteps) {
+  using R = Resident<NG>;
+  constexpr bool F32 = std::is_same<Real, float>::value;
+  constexpr int GH = WALLS ? 3 : 0;
+  __shared__ ResidentLds<Real, NG> sm;
+  const InstDesc& d = ba.inst[blockIdx.x];
+  BatchArgs b0 = ba;
+  b0.stage = 0;
+  StageArgs a = stage_args(b0, d);
+  const int nx = a.g.nx, ny = a.g.ny, P = nx * ny;
+  const int tid = threadIdx.x, group = __builtin_amdgcn_readfirstlane(tid / R::NODES), i = tid - group * R::NODES;
+  const bool active = i < P, rows = group < 5, moments = group == (R::GROUPS == 7 ? 5 : 2),
+             forces = group == (R::GROUPS == 7 ? 6 : 2);
+  const int ky = rows ? group : 0, mv = ky - (ky > 2 ? 1 : 0);   // moving row
+  const bool do_x = nx > 1, do_y = WALLS || ny > 1;
+  const int n = active ? i : 0, y = n / nx, x = n - y * nx;
+  const int own = n + GH * nx;
+  // places of the six values around the left face and of the five, in upwind
+  // order, of the lower face; the faces on the other side
+  int xo[6], yo[5];
+#pragma unroll
+  for (int j = 0; j < 6; ++j) xo[j] = own - x + wrap_near(x - 3 + j, nx);
+#pragma unroll
+  for (int j = 0; j < 5; ++j) {
+    const int r = ky > 2 ? j - 3 : 2 - j;
+    yo[j] = WALLS ? own + r * nx : wrap_near(y + r, ny) * nx + x;
+  }
+  const int xr = n - x + (x + 1 < nx ? x + 1 : 0), yu = WALLS ? n + nx : (y + 1 < ny ? n + nx : x);
+  // neighbours in the carried fields (columns -3 .. 3, rows -3 .. 3)
+  if (forces) {
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+      sm.cc[j][i] = wrap_near(x + j - 3, nx);
+      const int r = y + j - 3;
+      sm.cr[j][i] = nx * (WALLS ? min(max(r < 0 ? -1 - r : r >= ny ? 2 * ny - 1 - r : r, 0), ny - 1) : wrap_near(r, ny));
+    }
+  }
+  const gmem<Real>* const f0 = as_global(reinterpret_cast<Real*>(d.f[0]));
+  const int64_t at = (int64_t)(y + 3) * a.g.rs + x;
+  Real out[5] = {};
+  if (rows) {
+#pragma unroll
+    for (int kx = 0; kx < 5; ++kx) out[kx] = f0[(5 * ky + kx) * a.g.ps + at];
+  }
+  MomSum fs;
+  double cn = 0.0, cdp = 0.0;
+  if (moments) {
+    cn = as_global(d.carry[ba.cur])[n];
+    cdp = as_global(d.carry[ba.cur])[P + n];
+  }
+  bool bad = false;
+  auto publish = [&]() {
+    if (rows && active) {
+#pragma unroll
+      for (int kx = 0; kx < 5; ++kx) sm.f[5 * ky + kx][own] = out[kx];
+    }
+    __syncthreads();
+  };
+  if (WALLS && tid < 2) sm.em[tid].set(d, tid);
+  publish();
+  if (moments) fs = node_sums([&](int k) { return sm.f[k][own]; });
+
+#pragma unroll 1
+  for (int step = 0; step < nsteps; ++step) {
+    Real fn[5];
+#pragma unroll
+    for (int kx = 0; kx < 5; ++kx) fn[kx] = out[kx];
+#pragma unroll 1
+    for (int s = 0; s < 3; ++s) {
+      a.A = s == 0 ? RK_A[0] : s == 1 ? RK_A[1] : RK_A[2];
+      a.B = s == 0 ? RK_B[0] : s == 1 ? RK_B[1] : RK_B[2];
+      auto mine = [&](int k) { return sm.f[k][own]; };
+      if (WALLS) {
+        // ghost rows: a lane per (population, side, column)
+        for (int e = tid; e < 50 * nx; e += R::THREADS) {
+          const int k = e / (2 * nx), sc = e - 2 * nx * k, side = sc >= nx ? 1 : 0, c = sc - side * nx;
+          const int first = side ? ny + 2 : 3, in = side ? -1 : 1;   // LDS row of the wall's lattice row
+          const WallSide w{side, first, first + in, first + 2 * in, {first - in, first - 2 * in, first - 3 * in}};
+          double rec;
+          wall_pass1<Real>(d, w, k, [&](int kk, int r) -> Real& { return sm.f[kk][r * nx + c]; }, rec);
+          const int j = side ? k / 5 - 3 : k / 5;
+          if (j == 0 || j == 1) sm.rec[side][5 * j + k % 5][c] = rec;
+        }
+        __syncthreads();
+        // a lane per (emitted population, side, column)
+        for (int e = tid; e < 20 * nx; e += R::THREADS) {
+          const int q = e / nx, c = e - q * nx, hi = q >= 10 ? 1 : 0, j = (q - 10 * hi) / 5, kx = q - 10 * hi - 5 * j;
+          double nw = 0.0;
+          if (hi || d.g.walls != 2) {
+            const WallEmission<Real>& em = sm.em[hi];
+            nw = em.density(d, hi, [&](int jj, int kk) { return sm.rec[hi][5 * jj + kk][c]; });
+            const Real v = em.value(d, hi, nw, kx, j);
+#pragma unroll
+            for (int r = 0; r < 3; ++r) sm.f[5 * (hi ? j : 3 + j) + kx][(hi ? ny + 3 + r : r) * nx + c] = v;
+          }
+          if (q - 10 * hi == 0) d.nw[hi * nx + c] = nw;
+        }
+        __syncthreads();
+      }
+      // faces; meanwhile the sums of the source (those of the last stage's
+      // result) and its carry
+      Real rxl[5] = {}, ryl[5] = {};
+      auto faces = [&](int from, int to) {
+#pragma unroll
+        for (int kx = 0; kx < 5; ++kx) {
+          if (kx < from || kx >= to) continue;
+          const Real* const q = sm.f[5 * ky + kx];
+          if (do_x && kx != 2) {
+            const Real c[6] = {q[xo[0]], q[xo[1]], q[xo[2]], q[xo[3]], q[xo[4]], q[xo[5]]};
+            rxl[kx] = face_value<Real>(a, c, kx > 2);
+            sm.xf[4 * ky + kx - (kx > 2 ? 1 : 0)][n] = rxl[kx];
+          }
+          if (do_y && ky != 2) {
+            ryl[kx] = face_value(a, q[yo[0]], q[yo[1]], q[yo[2]], q[yo[3]], q[yo[4]]);
+            sm.yf[5 * mv + kx][n] = ryl[kx];
+          }
+          keep_order(rxl[kx], ryl[kx]);
+        }
+      };
+      if (moments && active) {
+        sm.cm[0][i] = cn;
+        sm.cm[1][i] = cdp;
+      }
+      if (rows && active) faces(0, 3);
+      __syncthreads();
+      if (moments && active) put_equilibrium<Real>(a, fs, [&](int j, Real v) { sm.eq[j][i] = v; });
+      if (forces && active) {
+        const double inv_nc = 1.0 / sm.cm[0][i];
+        int cc[7], cr[7];
+#pragma unroll
+        for (int j = 0; j < 7; ++j) {
+          cc[j] = sm.cc[j][i];
+          cr[j] = sm.cr[j][i];
+        }
+        auto pp = [&](int l, int m) { return sm.cm[1][cr[m + 3] + cc[l + 3]]; };
+        auto nn = [&](int l, int m) { return sm.cm[0][cr[m + 3] + cc[l + 3]]; };
+        if (do_x) sm.F[0][i] = node_force(a, inv_nc, pp, nn);
+        if (do_y)
+          sm.F[1][i] = node_force(a, inv_nc, [&](int l, int m) { return pp(m, l); },
+                                  [&](int l, int m) { return nn(m, l); });
+      }
+      if (rows && active) faces(3, 5);
+      if (WALLS && rows && ky != 2 && i < 5 * nx) {
+        // the faces above the last row: lane (kx, x)
+        const int kx = i / nx, c = i - kx * nx;
+        const Real* const q = sm.f[5 * ky + kx] + (ky > 2 ? ny : ny + 5) * nx + c;
+        const int st = ky > 2 ? nx : -nx;
+        sm.yf[5 * mv + kx][P + c] = face_value(a, q[0], q[st], q[2 * st], q[3 * st], q[4 * st]);
+      }
+      __syncthreads();
+      if (rows && active) {
+        Real acc[5], adv[5];
+        const Real p = (Real)row_tables.p[ky];
+#pragma unroll
+        for (int kx = 0; kx < 5; ++kx) {
+          acc[kx] = (Real)a.A * fn[kx];
+          adv[kx] = 0;
+          if (do_x && kx != 2)
+            adv[kx] = (Real)Rk[kx] * (sm.xf[4 * ky + kx - (kx > 2 ? 1 : 0)][xr] - rxl[kx]);
+          if (do_y && ky != 2) adv[kx] = fmadd(p, sm.yf[5 * mv + kx][yu] - ryl[kx], adv[kx]);
+        }
+        row_terms<Real>(a, ky, do_x ? sm.F[0][i] : 0.0, do_y ? sm.F[1][i] : 0.0, acc, adv,
+                        [&](int sy, int kx) { return sm.f[5 * sy + kx][own]; });
+#pragma unroll
+        for (int kx = 0; kx < 5; ++kx)
+          out[kx] = with_equilibrium<Real>(a, acc[kx], kx, ky, [&](int j) { return sm.eq[j][i]; });
+      }
+      __syncthreads();   // every read of the source is done
+      publish();
+      if (moments && active) {
+        fs = node_sums(mine);
+        carry_finish<F32>(fs, a.rho0, a.tref, a.a, a.b, cn, cdp);
+        if (!(fabs(cn) < INFINITY)) bad = true;
+      }
+    }
+  }
+  if (rows && active) {
+    gmem<Real>* const fd = as_global(reinterpret_cast<Real*>(d.f[0]));
+#pragma unroll
+    for (int kx = 0; kx < 5; ++kx) fd[(5 * ky + kx) * a.g.ps + at] = out[kx];
+  }
+  if (moments && active) {
+    gmem<double>* const co = as_global(d.carry[ba.cur ^ (nsteps & 1)]);
+    co[n] = cn;
+    co[P + n] = cdp;
+    if (bad) ba.flag[0] = 1;
+  }
 }
 
 }  // namespace olbk

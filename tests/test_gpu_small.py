@@ -1,6 +1,7 @@
 """Small lattices: the kernels that update them (16 x 8 tiles split by
-velocity rows, wall ghosts formed in the tile) against the stage kernel,
-which a chosen tile height selects.  Every node's sums are taken in the same
+velocity rows, wall ghosts formed in the tile; whole steps in one workgroup
+for lattices of up to 192 nodes) against the stage kernel, which a chosen
+tile height selects.  Every node's sums are taken in the same
 order by both, so f, the moments and the wall densities agree to the bit."""
 import numpy as np
 import pytest
@@ -32,7 +33,12 @@ CASES = ([("noisy", s) for s in ((1, 1), (5, 3), (16, 8), (17, 9), (15, 7), (33,
          + [("half", s) for s in ((5, 3), (16, 9), (40, 70))]
          + [("box0", s) for s in ((3, 12), (17, 8), (70, 37))]
          + [("box1", s) for s in ((3, 5), (16, 16), (35, 19))]
-         + [("box2", s) for s in ((3, 4), (16, 8), (70, 13))])
+         + [("box2", s) for s in ((3, 4), (16, 8), (70, 13))]
+         # one workgroup per lattice: 64, 128 and 192 nodes, ghost rows included
+         # 80, 144 and 208 places; the last that fits each and the first that does not
+         + [("noisy", s) for s in ((1, 60), (64, 1), (65, 1), (8, 16), (129, 1), (3, 64), (193, 1))]
+         + [("channel", s) for s in ((8, 4), (1, 160), (1, 186), (1, 187), (2, 40), (23, 3), (24, 3))]
+         + [("half", s) for s in ((1, 40), (16, 3), (7, 17))])
 
 
 def _case(kind, nx, ny):
@@ -96,3 +102,35 @@ def test_batch_of_small_lattices_equals_the_stage_kernel():
         for x, y in zip(got[0], other):
             for u, v in zip(x, y):
                 np.testing.assert_array_equal(u, v)
+
+
+@pytest.mark.parametrize("kind", ["waves", "columns"])
+def test_resident_batch_steps_and_graphs(kind):
+    """Batches of one-dimensional lattices: odd and long step counts (more than
+    one launch holds) and graph replays give the stage kernel's bits."""
+    olb = _olb()
+    if kind == "waves":
+        cases = [I.shear_wave(n, 0.3 * i, *m) for i, (n, m) in enumerate(
+            ((20, (1.0, 0.0, 0.0, 0.0)), (60, (1.9327, 9 / 8, 1 / 3, 1e-4)), (33, (0.2397, 9 / 8, 1 / 3, 1e-4))))]
+    else:
+        cases = [I.planar_interface(tw, 0.2397, 1.9327, cells=c) for tw, c in ((0.8, 160), (0.85, 47), (0.9, 100))]
+    got = []
+    for by, graph in ((8, 0), (None, 0), (None, 4)):
+        b = olb.Batch([c.params for c in cases])
+        if by:
+            b.set_tile(by)
+        if graph:
+            b.use_graph(graph)
+        for i, c in enumerate(cases):
+            b.set_fields(i, *c.fields)
+        out = []
+        for steps in (4, 3, 1, 260):
+            b.step(steps)
+            out += [b.get_f(i) for i in range(len(cases))]
+            if kind == "columns":
+                out += [w for i in range(len(cases)) for w in b.wall_density(i)]
+        got.append(out)
+        b.close()
+    for other in got[1:]:
+        for u, v in zip(got[0], other):
+            np.testing.assert_array_equal(u, v)

@@ -418,8 +418,12 @@ struct Fp32Equilibrium {
 #endif
 template <typename Real>
 constexpr int min_waves_per_simd() { return std::is_same<Real, float>::value ? OLB_WAVES32 : OLB_WAVES64; }
-template <typename Real>
-constexpr int prefetch_depth() { return std::is_same<Real, float>::value ? OLB_PREFETCH32 : OLB_PREFETCH64; }
+// (the FP64 specular-x variants too: at full depth they take 130 registers, and
+// past 128 a CU runs one workgroup instead of two)
+template <typename Real, bool XSPEC>
+constexpr int prefetch_depth() {
+  return std::is_same<Real, float>::value ? OLB_PREFETCH32 : OLB_PREFETCH64 - (XSPEC ? 1 : 0);
+}
 
 template <typename Real, int BY, bool WALLS, bool FN, bool XSPEC>
 __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, const int y0,
@@ -501,21 +505,16 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
   }
   const int ownb = own * RB;
 
-  // Pointer views of the source array and the carried fields, for the
-  // specular-x loads (the other accesses go through buffer resources).  No
-  // __restrict__ anywhere: in the last RK stage f^n and f_dst are the same
-  // array (each node's f^n is read before its f_dst is written, by the same
-  // thread).
+  // Pointer view of the source array for the specular-x halo (the other
+  // accesses go through buffer resources).  No __restrict__ anywhere: in the
+  // last RK stage f^n and f_dst are the same array (each node's f^n is read
+  // before its f_dst is written, by the same thread).
   const gmem<const Real>* src = as_global(reinterpret_cast<const Real*>(a.fsrc));
-  const gmem<const Real>* fnp = as_global(reinterpret_cast<const Real*>(a.fn));
-  gmem<Real>* dst = as_global(reinterpret_cast<Real*>(a.fdst));
-  const gmem<const double>* cin = as_global(a.cin);
-  gmem<double>* cout = as_global(a.cout);
 
   constexpr int G = pop_group<Real>();
   static_assert(12 % G == 0, "population 12 must start a group: the moment sums take the populations in order");
   constexpr int NB = 2 * G;
-  constexpr int PF = prefetch_depth<Real>() - 1;
+  constexpr int PF = prefetch_depth<Real, XSPEC>() - 1;
   static_assert(PF >= G, "the register ring must hold the next group");
   auto tile_pop = [](int t) { return t < 12 ? t : t + 1; };
   // storage offset of population k at tile slot s (mirrored populations past
@@ -548,17 +547,11 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
   __builtin_amdgcn_sched_barrier(0);
   double cn_in[SLOTS], cp_in[SLOTS];
   {
-    const int64_t N = (int64_t)nx * ny;
     const __amdgpu_buffer_rsrc_t rn = plane_rsrc(a.cin, 0, cbytes), rp = plane_rsrc(a.cin, 1, cbytes);
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) {
-      if constexpr (XSPEC) {
-        cn_in[s] = cin[moff[s]];
-        cp_in[s] = cin[N + moff[s]];
-      } else {
-        cn_in[s] = bload<double>(rn, moffb[s]);
-        cp_in[s] = bload<double>(rp, moffb[s]);
-      }
+      cn_in[s] = bload<double>(rn, moffb[s]);
+      cp_in[s] = bload<double>(rp, moffb[s]);
     }
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -567,7 +560,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) pre[t % PF][s] = ld_src(tile_pop(t), s);
   // population 12 (p = 0 on both axes) needs no halo: read its own value
-  const Real f12 = XSPEC ? src[12 * ps + own] : bload<Real>(plane_rsrc(a.fsrc, 12, pbytes, rbytes), ownb);
+  const Real f12 = bload<Real>(plane_rsrc(a.fsrc, 12, pbytes, rbytes), ownb);
 
   auto plane = [&](int t) { return pl0 + (t % NB) * PO; };
 #pragma unroll
@@ -650,7 +643,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
   Real fnv[25];
 #pragma unroll
   for (int k = 0; k < 25; ++k)
-    fnv[k] = !use_fn ? (Real)0 : XSPEC ? fnp[k * ps + own] : bload<Real>(plane_rsrc(a.fn, k, pbytes, rbytes), ownb);
+    fnv[k] = !use_fn ? (Real)0 : bload<Real>(plane_rsrc(a.fn, k, pbytes, rbytes), ownb);
 
   // stage the second group and refill the ring behind it
 #pragma unroll
@@ -841,25 +834,16 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
       out = (Real)__builtin_fmaf(q.px[kx], q.by[ky], __builtin_fmaf(q.qx[kx], q.hy_w[ky], (float)acc[k]));
     else
       out = (Real)fmadd(cfe, (sn * (Wk[kx] * (1.0 + hx[kx]))) * (Wk[ky] * (1.0 + hy[ky])), (double)acc[k]);
-    if (active) {
-      if constexpr (XSPEC) dst[k * ps + own] = out;
-      else bstore<Real>(out, plane_rsrc(a.fdst, k, pbytes, rbytes), ownb);
-    }
+    if (active) bstore<Real>(out, plane_rsrc(a.fdst, k, pbytes, rbytes), ownb);
     dsum.add(k, (double)out);
   }
 
   if (active) {
     double cn, cdp;
     carry_finish<F32>(dsum, a.rho0, a.tref, a.a, a.b, cn, cdp);
-    const int64_t N = (int64_t)nx * ny;
     const int m = y * nx + x;
-    if constexpr (XSPEC) {
-      cout[m] = cn;
-      cout[N + m] = cdp;
-    } else {
-      bstore<double>(cn, plane_rsrc(a.cout, 0, cbytes), m * 8);
-      bstore<double>(cdp, plane_rsrc(a.cout, 1, cbytes), m * 8);
-    }
+    bstore<double>(cn, plane_rsrc(a.cout, 0, cbytes), m * 8);
+    bstore<double>(cdp, plane_rsrc(a.cout, 1, cbytes), m * 8);
     if (!(fabs(cn) < INFINITY)) a.flag[0] = 1;
   }
 }
@@ -937,10 +921,6 @@ __global__ void __launch_bounds__(64 * BY, min_waves_per_simd<Real>()) stage_ker
   stage_tile<Real, BY, WALLS, FN, XSPEC>(a, tile_x * TILE_X, tile_y * BY, sm);
 }
 
-// --------------------------------------------------------------------------
-// diffuse-reflection ghosts (Sec. 3.4.2, walls across y)
-// --------------------------------------------------------------------------
-
 // Quadratic extrapolation through a wall from the three interior rows next to
 // it (v0 adjacent): the ghost rows e1, e2, e3, nearest first.
 template <typename Real>
@@ -950,9 +930,25 @@ __device__ __forceinline__ void wall_extrapolate(Real v0, Real v1, Real v2, Real
   e3 = fmadd((Real)10, v0, fmadd((Real)-15, v1, (Real)6 * v2));
 }
 
+}  // namespace olbk
+
+#include "olb_split.hpp"
+
+namespace olbk {
+
+// --------------------------------------------------------------------------
+// diffuse-reflection ghosts (Sec. 3.4.2, walls across y)
+// --------------------------------------------------------------------------
+
+// A block takes 64 columns of one wall, a wave per velocity row: each thread
+// the five populations of its row.  One thread for all 25 took 12 us for 13
+// half channels and 21 us for ten 160-wide boxes, a chain of memory latencies
+// (the stores of one population's ghosts order the loads of the next); here
+// every load is issued before the first store.
 template <typename Real>
-__global__ void walls_kernel(const WallBatchArgs wa) {
-  constexpr bool F32 = std::is_same<Real, float>::value;
+__global__ void __launch_bounds__(320) walls_kernel(const WallBatchArgs wa) {
+  __shared__ double rec_sh[10][64];
+  __shared__ WallEmission<Real> em;
   // instance of this 64-column block (wall_block_base is ascending)
   int lo = 0, hi = wa.ninst - 1;
   const int blk = blockIdx.x;
@@ -961,104 +957,63 @@ __global__ void walls_kernel(const WallBatchArgs wa) {
     if (wa.inst[mid].wall_block_base <= blk) lo = mid; else hi = mid - 1;
   }
   const InstDesc& d = wa.inst[lo];
-  const int x = (blk - d.wall_block_base) * 64 + threadIdx.x;
+  const int tx = threadIdx.x, ky = __builtin_amdgcn_readfirstlane(threadIdx.y);
+  const int x = (blk - d.wall_block_base) * 64 + tx;
   const int wall = blockIdx.y;  // 0: lower wall (y = -1/2), 1: upper wall
   const int nx = d.g.nx, ny = d.g.ny;
-  if (x >= nx) return;
-  Real* __restrict__ f = reinterpret_cast<Real*>(d.f[wa.stage]);
+  const bool in = x < nx;
+  gmem<Real>* const f = as_global(reinterpret_cast<Real*>(d.f[wa.stage])) + (in ? x : 0);
   const int64_t ps = d.g.ps, rs = d.g.rs;
-  // storage rows: interior y -> y + 3
-  const int r0 = wall ? ny + 2 : 3, r1 = wall ? ny + 1 : 4, r2 = wall ? ny : 5;
-  const int g1 = wall ? ny + 3 : 2, g2 = wall ? ny + 4 : 1, g3 = wall ? ny + 5 : 0;
-  const double Tw = wall ? d.tw[1] : d.tw[0];
-  const double uw = wall ? d.uw[1] : d.uw[0];
-  const double rho0 = d.rho0;
-  // per-axis factors of the FP32 departure base
-  double bw[5];
-  {
-    double h0[5];
-    base_h0(d.tref, h0);
+  // storage rows (interior y -> y + 3): the wall's first lattice row, and the
+  // step into the lattice
+  const int r0 = wall ? ny + 2 : 3, st = wall ? -1 : 1;
+  const bool mirror = !wall && d.g.walls == 2, towards = wall ? ky >= 2 : ky <= 2;
+  const int j = wall ? ky - 3 : ky;            // which of the two rows moving towards the wall
+  const int from = mirror ? 4 - ky : ky;
+  Real e[5][3];
+  if (mirror || towards) {
+    Real v[5][3];
 #pragma unroll
-    for (int i = 0; i < 5; ++i) bw[i] = Wk[i] * (1.0 + h0[i]);
-  }
-  if (wall == 0 && d.g.walls == 2) {
-    // specular symmetry plane (Sec. 3.4.1): ghost row -1 - j of population
-    // (kx, ky) is interior row j of (kx, 4 - ky); the FP32 departure base is
-    // even in p_y, so the departure values mirror the same way
+    for (int kx = 0; kx < 5; ++kx)
 #pragma unroll
-    for (int k = 0; k < 25; ++k) {
-      const int km = 5 * (4 - k / 5) + k % 5;
-      const Real* src = f + km * ps + x;
-      Real* pk = f + k * ps + x;
-      pk[g1 * rs] = src[r0 * rs];
-      pk[g2 * rs] = src[r1 * rs];
-      pk[g3 * rs] = src[r2 * rs];
-    }
-    d.nw[x] = 0.0;
-    return;
-  }
-
-  // populations travelling towards the wall (and p_y = 0): quadratic
-  // extrapolation; their WENO flux through the wall face
-  double out = 0.0;
-#pragma unroll
-  for (int ky = 0; ky < 5; ++ky) {
-    const bool towards = wall ? (ky >= 2) : (ky <= 2);
-    if (!towards) continue;
+      for (int q = 0; q < 3; ++q) v[kx][q] = f[(5 * from + kx) * ps + (r0 + q * st) * rs];
 #pragma unroll
     for (int kx = 0; kx < 5; ++kx) {
-      const int k = 5 * ky + kx;
-      Real* pk = f + k * ps + x;
-      const Real v0 = pk[r0 * rs], v1 = pk[r1 * rs], v2 = pk[r2 * rs];
-      Real e1, e2, e3;
-      wall_extrapolate(v0, v1, v2, e1, e2, e3);
-      pk[g1 * rs] = e1;
-      pk[g2 * rs] = e2;
-      pk[g3 * rs] = e3;
-      if (ky != 2) {
-        // face between the adjacent interior row and the first ghost row;
-        // upwind order (far interior ... ghost) is the same at both walls
-        double rec = (double)weno_rec(v2, v1, v0, e1, e2);
-        if (F32) rec = fmadd(bw[kx] * bw[ky], rho0, rec);
-        out = fmadd(Rk[ky], rec, out);
+      if (mirror) {
+        // specular symmetry plane (Sec. 3.4.1): ghost row -1 - j of population
+        // (kx, ky) is interior row j of (kx, 4 - ky); the FP32 departure base
+        // is even in p_y, so the departure values mirror the same way
+#pragma unroll
+        for (int q = 0; q < 3; ++q) e[kx][q] = v[kx][q];
+      } else {
+        // populations travelling towards the wall (and p_y = 0): quadratic
+        // extrapolation; their WENO value at the wall face (upwind order, far
+        // interior ... ghost, is the same at both walls)
+        wall_extrapolate(v[kx][0], v[kx][1], v[kx][2], e[kx][0], e[kx][1], e[kx][2]);
+        if (ky != 2) rec_sh[5 * j + kx][tx] = (double)weno_rec(v[kx][2], v[kx][1], v[kx][0], e[kx][0], e[kx][1]);
       }
     }
   }
-  // Eq. nw: the denominator sums g_kx(u_w, T_w) g_ky(0, T_w) p_ky over the
-  // wall-emitted velocities; sum_kx g_kx = 1 leaves sum_ky g_ky(0, T_w) p_ky.
-  double hx[5], hy[5];
-  hfac(uw, Tw - 1.0, hx);
-  hfac(0.0, Tw - 1.0, hy);
-  double den = 0.0;
-#pragma unroll
-  for (int ky = 0; ky < 5; ++ky) {
-    const bool emitted = wall ? (ky < 2) : (ky > 2);
-    if (emitted) den = fmadd(Wk[ky] * (1.0 + hy[ky]), Rk[ky], den);
-  }
-  const double nw = -out / den;
-  d.nw[wall * nx + x] = nw;
-#pragma unroll
-  for (int ky = 0; ky < 5; ++ky) {
-    const bool emitted = wall ? (ky < 2) : (ky > 2);
-    if (!emitted) continue;
+  if (threadIdx.x == 0 && ky == 2) em.set(d, wall);
+  __syncthreads();
+  double nw = 0.0;
+  const int je = wall ? ky : ky - 3;           // which of the two emitted rows
+  if (!mirror && (je == 0 || je == 1)) {
+    nw = em.density(d, wall, [&](int jj, int kx) { return rec_sh[5 * jj + kx][tx]; });
 #pragma unroll
     for (int kx = 0; kx < 5; ++kx) {
-      const int k = 5 * ky + kx;
-      double v = (nw * (Wk[kx] * (1.0 + hx[kx]))) * (Wk[ky] * (1.0 + hy[ky]));
-      if (F32) v = fmadd(-(bw[kx] * bw[ky]), rho0, v);
-      Real* pk = f + k * ps + x;
-      pk[g1 * rs] = (Real)v;
-      pk[g2 * rs] = (Real)v;
-      pk[g3 * rs] = (Real)v;
+      const Real v = em.value(d, wall, nw, kx, je);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) e[kx][q] = v;
     }
   }
+  if (!in) return;
+#pragma unroll
+  for (int kx = 0; kx < 5; ++kx)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) f[(5 * ky + kx) * ps + (r0 - (q + 1) * st) * rs] = e[kx][q];
+  if (je == 0) d.nw[wall * nx + x] = nw;
 }
-
-}  // namespace olbk
-
-#include "olb_split.hpp"
-
-namespace olbk {
 
 // --------------------------------------------------------------------------
 // set-up and read-out
@@ -1245,7 +1200,7 @@ hipError_t launch_resident(const BatchArgs& a, int nsteps, int ng, int real_byte
 }
 
 hipError_t launch_walls(const WallBatchArgs& a, int real_bytes, int wall_blocks, hipStream_t s) {
-  dim3 block(64), grid(wall_blocks, 2);
+  dim3 block(64, 5), grid(wall_blocks, 2);
   if (real_bytes == 8)
     hipLaunchKernelGGL(walls_kernel<double>, grid, block, 0, s, a);
   else

@@ -165,20 +165,21 @@ struct Engine {
 
   // Which kernel takes the stages, unless the caller chose a tile height: the
   // split kernel while the stage kernel's tiles leave it the slower one.  A
-  // stage kernel tile costs the chip about three split tiles (FP64: 1024^2
-  // takes 8192 split tiles 220 us, 2176 stage tiles 175 us; FP32: 143 and
-  // 97 us), but a launch of it takes 21 us (FP32 17) however few tiles it has,
-  // about 800 split tiles' time, where a launch of the split kernel takes 9.
-  // Walls cost the stage kernel a launch of their own (8 us and more), and its
-  // specular-x variants run one workgroup per CU instead of two.
+  // stage kernel tile costs the chip about three split tiles (FP64: a stage of
+  // 512^2 takes 50 us either way, in 576 stage or 2048 split tiles, one of
+  // 1024^2 175 us in 2176 stage and 220 in 8192 split tiles; FP32, 320 x 640:
+  // 26 us in 480 and 27 in 1600), but a launch of it takes 21 us (FP32 17)
+  // however few tiles it has, about 800 split tiles' time, where a launch of
+  // the split kernel takes 9.  Walls cost the stage kernel a launch of their
+  // own, 4 us.
   bool split_is_faster() const {
     int64_t ts = 0, tq = 0;
     for (const auto& q : p) {
       ts += tile_count(q, olbk::SPLIT_X, olbk::SPLIT_Y);
       tq += tile_count(q, olbk::TILE_X, 8);
     }
-    const double per_tile = (rb == 8 ? 3.0 : 2.5) * (xspec ? 1.5 : 1.0);
-    return (double)ts <= std::max(800.0, per_tile * (double)tq) + (walls ? 300.0 : 0.0);
+    const double per_tile = rb == 8 ? 3.0 : 2.5;
+    return (double)ts <= std::max(800.0, per_tile * (double)tq) + (walls ? 150.0 : 0.0);
   }
 
   // NG of the resident kernel that holds every instance whole, or 0

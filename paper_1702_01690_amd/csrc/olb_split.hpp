@@ -235,8 +235,10 @@ __device__ __forceinline__ void wall_pass1(const InstDesc& d, const WallSide& w,
   if (ky != 2) rec = (double)weno_rec(v2, v1, v0, e[0], e[1]);
 }
 
-// pass 2: n_w of a column (recs(ky, kx): its wall-face values), and the value
-// of an emitted population
+// pass 2: n_w of a column (Eq. nw; recs(j, kx): its wall-face values; the
+// denominator sums g_kx(u_w, T_w) g_ky(0, T_w) p_ky over the wall-emitted
+// velocities, and sum_kx g_kx = 1 leaves sum_ky g_ky(0, T_w) p_ky), and the
+// value of an emitted population
 template <typename Real>
 struct WallEmission {
   static constexpr bool F32 = std::is_same<Real, float>::value;

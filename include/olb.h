@@ -247,11 +247,12 @@ void olb_batch_free(olb_batch* b);
  * with W[co][ci][ky][kx] weighting input (x + kx - 1, y + ky - 1).
  *
  * Moment planes are device double [4][ny][nx] (n, u_x, u_y, T), y outer.
- * A closure object holds no device memory of its own: the caller's
- * workspace (256-byte aligned, olb_closure_workspace_bytes) keeps
- * activations, parameters, gradients, Adam state and the per-workgroup
- * partial sums of the reductions over nodes.  Work is enqueued on
- * hip_stream; calls that return host values synchronise it.
+ * A closure object holds no device memory of its own (but 46 KB of
+ * page-locked host memory for gradients and loss): the caller's workspace
+ * (256-byte aligned, olb_closure_workspace_bytes) keeps activations,
+ * parameters, Adam state and the per-workgroup partial sums of the reductions
+ * over nodes.  Work is enqueued on hip_stream; calls that return host values
+ * synchronise it.
  * ------------------------------------------------------------------------ */
 #define OLB_CLOSURE_NPARAM 11588
 typedef struct olb_closure olb_closure;
@@ -270,8 +271,8 @@ olb_status olb_closure_get_params(olb_closure* c, float* params);
  * [4][ny][nx] (double), scaled by out_scale and projected as set by
  * olb_closure_set_conserve.  Asynchronous.  OLB_E_STATE before set_params. */
 olb_status olb_closure_forward(olb_closure* c, const double* dev_moments, double* dev_delta);
-/* The same through the training path's kernels (one launch per layer, the
- * activations in the workspace) instead of the fused one-tile-per-workgroup
+/* The same layer by layer (one launch per layer, the activations in the
+ * workspace) instead of the fused one-tile-per-workgroup
  * kernel; without projection (mask 0) the two agree to the bit, with it to
  * FP64 rounding of the channel sums (which the two add in different
  * orders). */

@@ -151,11 +151,10 @@ __device__ __forceinline__ bf16x8 b_frag(const bf16* row_k0) {
 // 16-byte reads).  A wave
 // computes FWD_MT tiles of 16 pixels x all output channels; for each tile all
 // activation loads are issued before its MFMAs (FWD_MT at most; fewer on small
-// lattices so that the grid still fills the chip).  STORE_Z keeps the FP32
-// pre-activation (the ReLU mask of the backward pass); STORE_A writes the bf16
-// activation (the next layer's input).
+// lattices so that the grid still fills the chip).  HIDDEN layers write the
+// bf16 activation (the next layer's input), the last one its FP32 output.
 constexpr int FWD_MT = 4;
-template <int CIN, int COUT, bool RELU, bool STORE_Z, bool STORE_A>
+template <int CIN, int COUT, bool HIDDEN>
 __global__ void __launch_bounds__(256) conv_fwd(const bf16* __restrict__ X, const bf16* __restrict__ Wt,
                                                 const float* __restrict__ bias, float* __restrict__ Z,
                                                 bf16* __restrict__ A, int nx, int ny, int mtw) {
@@ -199,203 +198,11 @@ __global__ void __launch_bounds__(256) conv_fwd(const bf16* __restrict__ X, cons
         const int p = p0 + 4 * g + v;
         if (p >= P) continue;
         const float z = acc[t][v] + bc;
-        if (STORE_Z) Z[(size_t)p * COUT + co] = z;
-        if (STORE_A) A[(size_t)p * COUT + co] = to_bf16(RELU ? fmaxf(z, 0.f) : z);
+        if (HIDDEN) A[(size_t)p * COUT + co] = to_bf16(fmaxf(z, 0.f));
+        else Z[(size_t)p * COUT + co] = z;
       }
     }
   }
-}
-
-// ----------------------------------------------------------- backward data --
-// dX[q][ci] = sum_{tap, co} G[q - off(tap)][co] Wt[co][tap * CIN + ci]; the
-// result is multiplied by the ReLU mask (Zprev > 0) of the layer below and
-// rounded to bf16: the gradient with respect to that layer's pre-activation.
-template <int CIN, int COUT>
-__global__ void __launch_bounds__(256) conv_bwd_data(const bf16* __restrict__ G, const bf16* __restrict__ Wt,
-                                                     const float* __restrict__ Zprev,
-                                                     bf16* __restrict__ Gprev, int nx, int ny) {
-  constexpr int K = 9 * COUT, KP = (K + 15) / 16 * 16, NT = (CIN + 15) / 16;
-  constexpr int WKP = kp_of(CIN);
-  const int P = nx * ny;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int q0 = (blockIdx.x * 4 + wave) * 16;
-  if (q0 >= P) return;
-  const int i = lane & 15, g = lane >> 4;
-  const Pix qa = pix_of(min(q0 + i, P - 1), nx);
-  f32x4 acc[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int ks = 0; ks < KP / 16; ++ks) {
-    const int k0 = ks * 16 + 4 * g;  // k = tap * COUT + co
-    bf16x4 a;
-    if (k0 < K) {
-      const int tap = k0 / COUT, co = k0 - tap * COUT;
-      // neighbour q - off(tap): the tap mirrored through the centre (8-byte load)
-      a = *reinterpret_cast<const bf16x4*>(G + (size_t)nbr(qa, 8 - tap, nx, ny) * COUT + co);
-    } else {
-      a = bf16x4{0, 0, 0, 0};
-    }
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      bf16x4 b;
-      const int ci = t * 16 + i;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int k = k0 + v;
-        if (k < K && ci < CIN) {
-          const int tap = k / COUT, co = k - tap * COUT;
-          b[v] = (short)Wt[(size_t)co * WKP + tap * CIN + ci];
-        } else {
-          b[v] = 0;
-        }
-      }
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[t], 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int ci = t * 16 + i;
-    if (ci >= CIN) continue;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int q = q0 + 4 * g + v;
-      if (q >= P) continue;
-      const size_t o = (size_t)q * CIN + ci;
-      Gprev[o] = to_bf16(Zprev[o] > 0.f ? acc[t][v] : 0.f);
-    }
-  }
-}
-
-// --------------------------------------------------------- backward weight --
-// dW[co][ci][tap] = sum_p G[p][co] X[p + off(tap)][ci]  (GEMM M = COUT,
-// N = 9 CIN, reduction over pixels).  Each wave owns one 16 x 16 output tile
-// (blockIdx.x picks 4 tiles) and reduces it over one pixel chunk
-// (blockIdx.y), whose partial sums it writes to row blockIdx.y of
-// dWp[chunk][COUT * CIN * 9]; sum_segments adds the rows in order.
-template <int CIN, int COUT>
-__global__ void __launch_bounds__(256) conv_bwd_weight(const bf16* __restrict__ G, const bf16* __restrict__ X,
-                                                       float* __restrict__ dWp, int nx, int ny, int chunk) {
-  constexpr int K = 9 * CIN, KP = (K + 15) / 16 * 16, MT = (COUT + 15) / 16, NTK = KP / 16;
-  constexpr int TILES = MT * NTK;
-  const int P = nx * ny;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int tile = blockIdx.x * 4 + wave;
-  if (tile >= TILES) return;
-  const int i = lane & 15, g = lane >> 4;
-  const int mt = tile / NTK, nt = tile - mt * NTK;
-  const int co = mt * 16 + i;             // A-operand row: output channel
-  const int k = nt * 16 + i;              // B-operand column: tap * CIN + ci
-  const int tap = k / CIN, ci = k - tap * CIN;
-  const bool co_ok = co < COUT, k_ok = k < K;
-  const int pbeg = blockIdx.y * chunk, pend = min(pbeg + chunk, P);
-  // two accumulators over alternate 16-pixel steps keep more loads in flight
-  f32x4 acc0 = f32x4{0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
-  // coordinates of this lane's 4 pixels in the current and the next step
-  Pix q[2][4];
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) q[h][v] = pix_of(min(pbeg + 16 * h + 4 * g + v, P - 1), nx);
-  for (int p0 = pbeg; p0 < pend; p0 += 32) {
-    bf16x4 a[2], b[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int p = p0 + 16 * h + 4 * g + v;
-        const bool ok = p < pend;
-        a[h][v] = (ok && co_ok) ? (short)G[(size_t)p * COUT + co] : (short)0;
-        b[h][v] = (ok && k_ok) ? (short)X[(size_t)nbr(q[h][v], tap, nx, ny) * CIN + ci] : (short)0;
-      }
-    acc0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[0], b[0], acc0, 0, 0, 0);
-    acc1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[1], b[1], acc1, 0, 0, 0);
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        q[h][v].x += 32;
-        while (q[h][v].x >= nx) {  // at most ceil(32 / nx) passes
-          q[h][v].x -= nx;
-          ++q[h][v].y;
-        }
-      }
-  }
-  const f32x4 acc = acc0 + acc1;
-  // lane holds D[4g + v][i]: output channel mt*16 + 4g + v, k = nt*16 + i
-  if (!k_ok) return;
-  float* row = dWp + (size_t)blockIdx.y * (COUT * CIN * 9);
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int c = mt * 16 + 4 * g + v;
-    if (c < COUT) row[(c * CIN + ci) * 9 + tap] = acc[v];
-  }
-}
-
-// Partial bias gradients dbp[block][c] = sum over the block's pixels of
-// G[p][c]: thread (row r, channel c) sums channel c over rows r, r + R, ...
-// (coalesced rows of C values), then one LDS reduction
-template <int C>
-__global__ void __launch_bounds__(256) bias_grad(const bf16* __restrict__ G, float* __restrict__ dbp, int P) {
-  constexpr int R = 256 / C;
-  __shared__ float part[256];
-  const int c = threadIdx.x % C, r = threadIdx.x / C;
-  float s = 0.f;
-  for (int p = blockIdx.x * R + r; p < P; p += gridDim.x * R) s += from_bf16(G[(size_t)p * C + c]);
-  part[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x < C) {
-    float t = 0.f;
-#pragma unroll
-    for (int j = 0; j < R; ++j) t += part[j * C + threadIdx.x];
-    dbp[(size_t)blockIdx.x * C + threadIdx.x] = t;
-  }
-}
-
-// Fixed-order sums of row-major partial sums: dst[j] = sum over rows r of
-// src[r * n + j], for up to 8 segments (blockIdx.y).  A block takes C columns
-// (the smallest power of two >= n, at most 256) and R = 256 / C row phases:
-// thread (r, c) adds rows r, r + R, ... in order, then a tree over the phases.
-// The order depends only on (rows, n), so every run gives the same bits.  The
-// rows are loaded 16 at a time before they are added, so that a thread waits
-// for one load latency per 16 rows rather than per row.
-struct SumSeg {
-  const float* src;
-  float* dst;
-  int rows, n;
-};
-struct SumSegs {
-  SumSeg s[8];
-};
-__global__ void __launch_bounds__(256) sum_segments(SumSegs segs) {
-  const SumSeg sg = segs.s[blockIdx.y];
-  int C = 256;
-  while (C > 1 && C / 2 >= sg.n) C >>= 1;
-  if ((int)blockIdx.x * C >= sg.n) return;  // the whole block: no column here
-  const int R = 256 / C, c = threadIdx.x % C, r = threadIdx.x / C;
-  const int col = blockIdx.x * C + c;
-  __shared__ float red[256];
-  constexpr int U = 16;
-  float acc = 0.f;
-  if (col < sg.n) {
-    const float* src = sg.src + col;
-    int row = r;
-    for (; row + (U - 1) * R < sg.rows; row += U * R) {
-      float v[U];
-#pragma unroll
-      for (int j = 0; j < U; ++j) v[j] = src[(size_t)(row + j * R) * sg.n];
-#pragma unroll
-      for (int j = 0; j < U; ++j) acc += v[j];
-    }
-    for (; row < sg.rows; row += R) acc += src[(size_t)row * sg.n];
-  }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int h = R / 2; h > 0; h >>= 1) {
-    if (r < h) red[r * C + c] += red[(r + h) * C + c];
-    __syncthreads();
-  }
-  if (r == 0 && col < sg.n) sg.dst[col] = red[c];
 }
 
 // Most partial sums of the projection (workgroups of output_sums and of
@@ -472,37 +279,11 @@ __global__ void prep_kernel(const double* __restrict__ m, int P, Norm nm, bf16* 
     x[(size_t)p * 4 + c] = to_bf16_int((float)((m[(size_t)c * P + p] - nm.in_mean[c]) * nm.in_inv_scale[c]));
 }
 
-// MSE loss on the normalised correction, whose target is (reference - m) /
-// out_scale; G3 = dL/dZ3 (bf16); lossp[block] = the block's share of the loss
-// (pixels blockIdx.x * 256 + threadIdx.x, stepping by the grid)
-__global__ void __launch_bounds__(256) loss_kernel(const float* __restrict__ Z3, const double* __restrict__ m,
-                                                   const double* __restrict__ ref, int P, Norm nm,
-                                                   bf16* __restrict__ G3, float* __restrict__ lossp) {
-  __shared__ float part[256];
-  const float scale = 2.0f / (4.0f * (float)P);
-  float l = 0.f;
-  for (int p = blockIdx.x * 256 + threadIdx.x; p < P; p += gridDim.x * 256) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const size_t o = (size_t)c * P + p;
-      const float t = (float)((ref[o] - m[o]) / nm.out_scale[c]);
-      const float d = Z3[(size_t)p * 4 + c] - t;
-      l += d * d;
-      G3[(size_t)p * 4 + c] = to_bf16(scale * d);
-    }
-  }
-  part[threadIdx.x] = l;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) lossp[blockIdx.x] = part[0] / (4.0f * (float)P);
-}
-
-// FP32 master parameters -> bf16 weight matrices (padded) of the three layers
+// FP32 master parameters -> bf16 weight matrices (padded) of the three layers,
+// and, unless T2 is null, those of the transposed convolutions of layers 2 and
+// 3: T[ci][tap * Cout + co] = W[co][ci][8 - tap]
 __global__ void pack_weights(const float* __restrict__ w, bf16* __restrict__ W1, bf16* __restrict__ W2,
-                             bf16* __restrict__ W3) {
+                             bf16* __restrict__ W3, bf16* __restrict__ T2, bf16* __restrict__ T3) {
   // layer l: Cin, Cout, offset of W in the flat vector
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   constexpr int KP1 = kp_of(4), KP2 = kp_of(32), KP3 = kp_of(32);
@@ -523,21 +304,16 @@ __global__ void pack_weights(const float* __restrict__ w, bf16* __restrict__ W1,
     float v = 0.f;
     if (co < 4 && k < 9 * 32) v = w[O3 + (co * 32 + k % 32) * 9 + k / 32];
     W3[j] = to_bf16(v);
+  } else if (T2 && idx < N1 + N2 + N3 + N2) {
+    const int j = idx - N1 - N2 - N3, ci = j / KP2, k = j - ci * KP2;
+    T2[j] = to_bf16(w[O2 + ((k % 32) * 32 + ci) * 9 + 8 - k / 32]);
+  } else if (T2 && idx < N1 + N2 + N3 + N2 + N1) {
+    const int j = idx - N1 - N2 - N3 - N2, ci = j / KP1, k = j - ci * KP1;
+    T3[j] = to_bf16(k < 9 * 4 ? w[O3 + ((k % 4) * 32 + ci) * 9 + 8 - k / 4] : 0.f);
   }
 }
-
-__global__ void adam_kernel(float* __restrict__ w, const float* __restrict__ g, float* __restrict__ m,
-                            float* __restrict__ v, int n, float lr, float b1, float b2, float eps,
-                            float c1, float c2) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  w[i] -= lr * (mi * c1) / (sqrtf(vi * c2) + eps);
-}
+constexpr int PACK_FORWARD = 32 * kp_of(4) + 32 * kp_of(32) + 16 * kp_of(32);
+constexpr int PACK_ALL = PACK_FORWARD + 32 * kp_of(32) + 32 * kp_of(4);
 
 // partial channel sums of the network output (double), for the conservative
 // projection: part[block][c] over pixels blockIdx.x * 256 + threadIdx.x,
@@ -689,33 +465,37 @@ __device__ __forceinline__ bf16x8 wfrag(const WeightFrags<CIN, COUT>& w, int ks,
 template <int CIN, int COUT>
 __device__ __forceinline__ bf16x8 wfrag(const WeightLds<CIN, COUT>& w, int ks, int t, int lane) { return w.frag(ks, t, lane); }
 
-template <int CIN, int COUT, int R, int IS, int RI, int PD, typename Wts, typename Epi>
+// ONE: a small region, one block (m-tile wave % MTILES, n-tile wave / MTILES)
+// per wave, without bias.
+template <int CIN, int COUT, int R, int IS, int RI, int PD, bool ONE = false, typename Wts, typename Epi>
 __device__ __forceinline__ void lds_layer(const bf16* in, const Wts& w, const BiasRegs<COUT>& bias,
                                           int wave, int lane, Epi epi) {
   constexpr int K = 9 * CIN, KP = kp_of(CIN), KS = KP / 32, NT = (COUT + 15) / 16;
-  constexpr int NPIX = R * R, MTILES = (NPIX + 15) / 16, MW = (MTILES + IW - 1) / IW;
+  constexpr int NPIX = R * R, MTILES = (NPIX + 15) / 16, MW = (MTILES + IW - 1) / IW, NW = ONE ? 1 : NT;
+  static_assert(!ONE || (NPIX % 16 == 0 && MTILES * NT == IW), "one block per wave");
+  const int wm = ONE ? wave % MTILES : wave, wt = ONE ? wave / MTILES : 0;
   static_assert(RI >= R + 2, "input rows hold the output row and its two halo columns");
   static_assert(COUT % 4 == 0, "four channels per lane");
   const int i = lane & 15, g = lane >> 4;
   int base[MW];  // this lane's activation row (region pixel) of each m-tile
 #pragma unroll
   for (int m = 0; m < MW; ++m) {
-    const int j = min((wave + IW * m) * 16 + i, NPIX - 1);
+    const int j = min((wm + IW * m) * 16 + i, NPIX - 1);
     const int r = j / R, c = j - r * R;
     base[m] = (r * RI + c) * IS;
   }
-  f32x4 acc[MW][NT];
+  f32x4 acc[MW][NW];
 #pragma unroll
   for (int m = 0; m < MW; ++m)
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < NW; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   // the fragments of K step ks + PD are read before the MFMAs of step ks
   // (a ring of PD + 1 fragment sets; the scheduling barriers keep that
   // order), so each step waits for reads issued PD steps earlier
   auto read_step = [&](int ks, bf16x8* b, bf16x8* a) {
     const int k0 = ks * 32 + 8 * g;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) b[t] = wfrag(w, ks, t, lane);
+    for (int t = 0; t < NW; ++t) b[t] = wfrag(w, ks, wt + t, lane);
 #pragma unroll
     for (int m = 0; m < MW; ++m) {
       auto at = [&](int tap, int ci) {
@@ -726,7 +506,7 @@ __device__ __forceinline__ void lds_layer(const bf16* in, const Wts& w, const Bi
     }
   };
   static_assert(PD >= 1, "prefetch depth");
-  bf16x8 b[PD + 1][NT], a[PD + 1][MW];
+  bf16x8 b[PD + 1][NW], a[PD + 1][MW];
 #pragma unroll
   for (int p = 0; p < PD && p < KS; ++p) read_step(p, b[p], a[p]);
 #pragma unroll
@@ -737,7 +517,7 @@ __device__ __forceinline__ void lds_layer(const bf16* in, const Wts& w, const Bi
 #pragma unroll
     for (int m = 0; m < MW; ++m)
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
+      for (int t = 0; t < NW; ++t)
         acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[cur][t], a[cur][m], acc[m][t], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -745,14 +525,15 @@ __device__ __forceinline__ void lds_layer(const bf16* in, const Wts& w, const Bi
   // region pixel mt*16 + i
 #pragma unroll
   for (int m = 0; m < MW; ++m) {
-    const int mt = wave + IW * m;
+    const int mt = wm + IW * m;
     if (mt >= MTILES) continue;
     const int q = mt * 16 + i;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int co = t * 16 + 4 * g;
+    for (int t = 0; t < NW; ++t) {
+      const int co = (wt + t) * 16 + 4 * g;
       if (co >= COUT || q >= NPIX) continue;
-      epi(q, co, f32x4{acc[m][t][0] + bias.b[t][0], acc[m][t][1] + bias.b[t][1], acc[m][t][2] + bias.b[t][2],
+      if (ONE) epi(q, co, acc[m][t]);
+      else epi(q, co, f32x4{acc[m][t][0] + bias.b[t][0], acc[m][t][1] + bias.b[t][1], acc[m][t][2] + bias.b[t][2],
                        acc[m][t][3] + bias.b[t][3]});
     }
   }
@@ -891,6 +672,370 @@ __global__ void __launch_bounds__(256) project_kernel(double* __restrict__ delta
     if ((mask >> c) & 1) delta[(size_t)c * P + p] -= red[c][0] / (double)P * (double)nm.out_scale[c];
 }
 
+// ------------------------------------------------------------- gradients --
+// Loss and gradient of one training pair, one pass over the lattice: for each
+// 8 x 8 tile the forward pass on the halo that its backward pass needs (input
+// on 18 x 18, layer 1 on 16 x 16, layer 2 on 14 x 14, output and loss gradient
+// g3 on 12 x 12), g2 on 10 x 10, g1 on the tile, every intermediate in LDS,
+// then the tile's share of all weight and bias gradients, which stays in
+// accumulator registers from tile to tile (a workgroup takes tiles blockIdx.x,
+// + gridDim.x, ...) and leaves as one row of partial sums per workgroup.
+// The layers are lds_layer's, with infer_kernel's bits; the transposed
+// convolutions are lds_layer on mirrored weights.  Halo recompute costs three
+// times the tile's forward products, which the matrix cores do in passing: the
+// bound is the chain of eight phases and their barriers.  Layer by layer this
+// took 13 launches, some gathering 2-byte operands across pixels.  A training
+// step without its loss read back, 128^2: 98 -> 22 us, 512^2: 517 -> 90;
+// gradients to the host, 128^2: 157 -> 36.
+//
+// Weight gradients, dW = sum over pixels of G (x) X: both operands are needed
+// pixel by pixel for fixed channels, the transpose of how they lie in LDS
+// ([pixel][channel]).  ds_read_b64_tr_b16 reads them that way: of each 16
+// lanes, lane l gives the address of four channels of pixel l / 4, and lane i
+// receives channel i of four pixels.  The addresses are free, so a tap is a
+// shift of the pixel, a pixel past the lattice's edge is a chunk of zeros, and
+// 16 columns may be four taps of four channels (layers 1 and 3, whose 36
+// (tap, channel) columns fill three blocks with one of ones left for the bias).
+constexpr int GT = 8;                                          // tile edge
+constexpr int GX = GT + 10, GA1 = GT + 8, GA2 = GT + 6, G3 = GT + 4, G2 = GT + 2;   // region edges
+// row strides: the width of the layer reading the region + 16 (see S0, S1)
+constexpr int GSX = GA1 + 16, GS1 = GA2 + 16, GS2 = G3 + 16, GS3 = G2 + 16, GSG = GT + 16;
+// partial sums: 7 blocks of 16 x 16 per wave
+constexpr int GRAD_SLOTS = 7, GRAD_ROW = GRAD_SLOTS * IW * 256;
+constexpr float ADAM_B1 = 0.9f, ADAM_B2 = 0.999f, ADAM_EPS = 1e-8f;
+constexpr int OFF_W1 = 0, OFF_B1 = 32 * 4 * 9, OFF_W2 = OFF_B1 + 32, OFF_B2 = OFF_W2 + 32 * 32 * 9,
+              OFF_W3 = OFF_B2 + 32, OFF_B3 = OFF_W3 + 4 * 32 * 9;
+
+struct GradLds {
+  __attribute__((aligned(16))) bf16 w2[32 * WL];
+  bf16 t2[32 * WL];
+  bf16 w3[16 * WL];
+  bf16 t3[32 * (kp_of(4) + 8)];
+  bf16 x0[GX * GSX * 4];
+  bf16 a1[GA1 * GS1 * HS];
+  bf16 a2[GA2 * GS2 * HS];
+  bf16 g3[G3 * GS3 * 4];
+  bf16 g2[G2 * GSG * HS];
+  bf16 g1[GT * GT * HS];
+  float t[G3 * G3][4];        // target of the normalised output
+  bf16 zero[4], one[4];
+  float loss[IW];
+};
+
+struct GradArgs {
+  const double *m, *ref;
+  Norm nm;
+  const bf16 *W1, *W2, *W3, *T2, *T3;
+  const float *b1, *b2, *b3;
+  int nx, ny;
+  float *rows, *lossp;
+};
+
+static constexpr int grad_tiles(int nx, int ny) { return ((nx + GT - 1) / GT) * ((ny + GT - 1) / GT); }
+// most rows of partial sums (workgroups)
+static int grad_rows(int nx, int ny) { return std::min(grad_tiles(nx, ny), MAX_PARTS); }
+
+__device__ __forceinline__ bf16x4 tr_read(const bf16* p) {
+  typedef __attribute__((address_space(3))) bf16x4 lds4;
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4*)(p));
+}
+__device__ __forceinline__ bf16x8 tr_frag(const bf16* lo, const bf16* hi) {
+  const bf16x4 a = tr_read(lo), b = tr_read(hi);
+  return __builtin_bit_cast(bf16x8, bf16x8s{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]});
+}
+
+__global__ void __launch_bounds__(64 * IW) grad_kernel(const GradArgs ga) {
+  __shared__ GradLds sm;
+  const int nx = ga.nx, ny = ga.ny, P = nx * ny;
+  const Norm& nm = ga.nm;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tiles_x = (nx + GT - 1) / GT, ntiles = tiles_x * ((ny + GT - 1) / GT);
+  stage_weights<32, kp_of(32)>(sm.w2, ga.W2, tid);
+  stage_weights<32, kp_of(32)>(sm.t2, ga.T2, tid);
+  stage_weights<16, kp_of(32)>(sm.w3, ga.W3, tid);
+  stage_weights<32, kp_of(4)>(sm.t3, ga.T3, tid);
+  if (tid < 4) {
+    sm.zero[tid] = 0;
+    sm.one[tid] = to_bf16(1.f);
+  }
+  WeightFrags<4, 32> wf1;
+  wf1.load(ga.W1, lane);
+  const WeightLds<32, 32> wl2{sm.w2}, wt2{sm.t2};
+  const WeightLds<32, 4> wl3{sm.w3};
+  const WeightLds<4, 32> wt3{sm.t3};
+  BiasRegs<32> bias1, bias2, none;
+  BiasRegs<4> bias3;
+  bias1.load(ga.b1, lane);
+  bias2.load(ga.b2, lane);
+  bias3.load(ga.b3, lane);
+  none.b[0] = none.b[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const float scale = 2.0f / (4.0f * (float)P);
+  float loss = 0.f;
+  f32x4 acc[GRAD_SLOTS];
+#pragma unroll
+  for (int j = 0; j < GRAD_SLOTS; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // region pixel (r, c) of an edge-R region around the tile at (tx0, ty0):
+  // its lattice pixel, periodic
+  auto pixel = [&](int tx0, int ty0, int halo, int r, int c) {
+    int gy = (ty0 - halo + r) % ny, gx = (tx0 - halo + c) % nx;
+    gy += gy < 0 ? ny : 0;
+    gx += gx < 0 ? nx : 0;
+    return (size_t)gy * nx + gx;
+  };
+  // threads 0 .. 323 carry the input pixels, threads 324 .. 467 the moments
+  // and the reference of the output pixels
+  constexpr int NX = GX * GX, N3 = G3 * G3;
+  static_assert(NX + N3 <= 64 * IW, "a pixel per thread");
+  double in[8];
+  auto load_tile = [&](int tile) {
+    const int ty0 = (tile / tiles_x) * GT, tx0 = (tile % tiles_x) * GT;
+    if (tid < NX) {
+      const size_t p = pixel(tx0, ty0, 5, tid / GX, tid % GX);
+#pragma unroll
+      for (int ch = 0; ch < 4; ++ch) in[ch] = ga.m[(size_t)ch * P + p];
+    } else if (tid < NX + N3) {
+      const int q = tid - NX;
+      const size_t p = pixel(tx0, ty0, 2, q / G3, q % G3);
+#pragma unroll
+      for (int ch = 0; ch < 4; ++ch) {
+        in[ch] = ga.m[(size_t)ch * P + p];
+        in[4 + ch] = ga.ref[(size_t)ch * P + p];
+      }
+    }
+  };
+  auto store_tile = [&]() {
+    if (tid < NX) {
+      bf16* const x = sm.x0 + ((tid / GX) * GSX + tid % GX) * 4;
+#pragma unroll
+      for (int ch = 0; ch < 4; ++ch) x[ch] = to_bf16_int((float)((in[ch] - nm.in_mean[ch]) * nm.in_inv_scale[ch]));
+    } else if (tid < NX + N3) {
+#pragma unroll
+      for (int ch = 0; ch < 4; ++ch) sm.t[tid - NX][ch] = (float)((in[4 + ch] - in[ch]) / nm.out_scale[ch]);
+    }
+  };
+
+  int tile = blockIdx.x;
+  load_tile(tile);
+  store_tile();
+  for (; tile < ntiles; tile += gridDim.x) {
+    const int ty0 = (tile / tiles_x) * GT, tx0 = (tile % tiles_x) * GT;
+    const int vy = min(GT, ny - ty0), vx = min(GT, nx - tx0);   // the tile's part of the lattice
+    __syncthreads();
+    lds_layer<4, 32, GA1, 4, GSX, PD1>(sm.x0, wf1, bias1, wave, lane, [&](int q, int co, f32x4 z) {
+      store_relu4(sm.a1 + (q / GA1 * GS1 + q % GA1) * HS + co, z);
+    });
+    __syncthreads();
+    lds_layer<32, 32, GA2, HS, GS1, PD2>(sm.a1, wl2, bias2, wave, lane, [&](int q, int co, f32x4 z) {
+      store_relu4(sm.a2 + (q / GA2 * GS2 + q % GA2) * HS + co, z);
+    });
+    __syncthreads();
+    lds_layer<32, 4, G3, HS, GS2, PD3>(sm.a2, wl3, bias3, wave, lane, [&](int q, int, f32x4 z) {
+      const int r = q / G3, c = q - r * G3;
+      const f32x4 t = *reinterpret_cast<const f32x4*>(sm.t[q]);
+      const f32x4 d = z - t;
+      typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+      *reinterpret_cast<u32x2*>(sm.g3 + (r * GS3 + c) * 4) =
+          u32x2{to_bf16x2(scale * d[0], scale * d[1]), to_bf16x2(scale * d[2], scale * d[3])};
+      if (r >= 2 && r < 2 + vy && c >= 2 && c < 2 + vx)
+        loss += d[0] * d[0] + d[1] * d[1] + d[2] * d[2] + d[3] * d[3];
+    });
+    __syncthreads();
+    // the ReLU mask of a hidden layer: its bf16 activation is positive
+    auto masked = [&](bf16* dst, const bf16* a, f32x4 z) {
+      const bf16x4 v = *reinterpret_cast<const bf16x4*>(a);
+      typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+      *reinterpret_cast<u32x2*>(dst) = u32x2{to_bf16x2(v[0] > 0 ? z[0] : 0.f, v[1] > 0 ? z[1] : 0.f),
+                                             to_bf16x2(v[2] > 0 ? z[2] : 0.f, v[3] > 0 ? z[3] : 0.f)};
+    };
+    lds_layer<4, 32, G2, 4, GS3, PD1>(sm.g3, wt3, none, wave, lane, [&](int q, int ci, f32x4 z) {
+      const int r = q / G2, c = q - r * G2;
+      masked(sm.g2 + (r * GSG + c) * HS + ci, sm.a2 + ((r + 2) * GS2 + c + 2) * HS + ci, z);
+    });
+    __syncthreads();
+    const int next = tile + gridDim.x;
+    if (next < ntiles) load_tile(next);
+    // layer 1's gradient: 4 x 16 pixels by 2 x 16 channels, one block per wave
+    lds_layer<32, 32, GT, HS, GSG, PD2, true>(sm.g2, wt2, none, wave, lane, [&](int q, int ci, f32x4 z) {
+      const int r = q / GT, c = q - r * GT;
+      masked(sm.g1 + q * HS + ci, sm.a1 + ((r + 4) * GS1 + c + 4) * HS + ci, z);
+    });
+    __syncthreads();
+    // weight gradients: K steps of 32 pixels (four rows of the tile); lane
+    // (i, g) reads chunk i % 4 of pixels i / 4 and 4 + i / 4 of row 4 s + g
+    const int i = lane & 15, g = lane >> 4, ch = (i & 3) * 4, px = i >> 2;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int r = 4 * s + g;
+      const bool in0 = r < vy && px < vx, in1 = r < vy && px + 4 < vx;
+      // A operand: 16 channels from c0 of the tile's pixels in a region whose
+      // tile starts at (h, h), zeros past the lattice
+      auto a_of = [&](const bf16* x, int rs, int h, int c0) {
+        const bf16* p = x + ((r + h) * rs + px + h) * HS + c0 + ch;
+        return tr_frag(in0 ? p : sm.zero, in1 ? p + 4 * HS : sm.zero);
+      };
+      // B operand of layer 2: tap nt / 2, channels 16 (nt & 1) .. + 15 of a1
+      auto b2_of = [&](int nt) {
+        const int tap = nt >> 1, ky = tap / 3, kx = tap - 3 * ky;
+        const bf16* p = sm.a1 + ((r + 3 + ky) * GS1 + px + 3 + kx) * HS + (nt & 1) * 16 + ch;
+        return tr_frag(p, p + 4 * HS);
+      };
+      // B operand of a four-channel array: taps 4 nt .. + 3 (lane's chunk: tap
+      // 4 nt + i % 4), shifted by sign times the tap's offset; chunk 9 is ones
+      auto b4_of = [&](const bf16* x, int rs, int h, int sign, int nt) {
+        const int tap = min(4 * nt + (i & 3), 9), ky = tap / 3, kx = tap - 3 * ky;
+        const bf16* p = x + ((r + h + sign * (ky - 1)) * rs + px + h + sign * (kx - 1)) * 4;
+        return tr_frag(tap < 9 ? p : sm.one, tap < 9 ? p + 16 : sm.one);
+      };
+      auto mma = [&](f32x4& c, bf16x8 a, bf16x8 b) { c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); };
+      const bf16x8 ga0 = a_of(sm.g2, GSG, 1, 0), ga1 = a_of(sm.g2, GSG, 1, 16);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const bf16x8 b = b2_of(wave + IW * j);
+        mma(acc[2 * j], ga0, b);
+        mma(acc[2 * j + 1], ga1, b);
+      }
+      // the other blocks, up to three per wave: 0 .. 3 the last two of layer
+      // 2, 4 .. 9 layer 3 (rows: its input channels), 10 .. 15 layer 1, 16 and
+      // 17 layer 2's bias, 18 layer 3's (the centre tap's columns against ones)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        const int id = wave + IW * j;
+        if (id < 4) {
+          mma(acc[4 + j], id & 1 ? ga1 : ga0, b2_of(16 + (id >> 1)));
+        } else if (id < 10) {
+          const int e = id - 4;
+          mma(acc[4 + j], a_of(sm.a2, GS2, 3, (e & 1) * 16), b4_of(sm.g3, GS3, 2, -1, e >> 1));
+        } else if (id < 16) {
+          const int e = id - 10;
+          mma(acc[4 + j], a_of(sm.g1, GT, 0, (e & 1) * 16), b4_of(sm.x0, GSX, 5, 1, e >> 1));
+        } else if (id < 18) {
+          mma(acc[4 + j], id & 1 ? ga1 : ga0, tr_frag(sm.one, sm.one));
+        } else if (id < 19) {
+          mma(acc[4 + j], tr_frag(in0 ? sm.one : sm.zero, in1 ? sm.one : sm.zero), b4_of(sm.g3, GS3, 2, -1, 1));
+        }
+      }
+    }
+    __syncthreads();
+    if (next < ntiles) store_tile();
+  }
+  float* const row = ga.rows + (size_t)blockIdx.x * GRAD_ROW;
+#pragma unroll
+  for (int j = 0; j < GRAD_SLOTS; ++j) *reinterpret_cast<f32x4*>(row + ((j * IW + wave) * 64 + lane) * 4) = acc[j];
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) loss += __shfl_xor(loss, o);
+  if (lane == 0) sm.loss[wave] = loss;
+  __syncthreads();
+  if (tid == 0) {
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < IW; ++w) t += sm.loss[w];
+    ga.lossp[blockIdx.x] = t / (4.0f * (float)P);
+  }
+}
+
+// Parameter whose gradient place c of a row holds, or -1: block (slot, wave),
+// lane (i, g), element v = row 4 g + v, column i of the block
+__device__ __forceinline__ int grad_param(int c) {
+  const int v = c & 3, lane = (c >> 2) & 63, wave = (c >> 8) % IW, slot = (c >> 8) / IW;
+  const int i = lane & 15, m = 4 * (lane >> 4) + v;
+  auto w2 = [&](int mt, int nt) {
+    const int n = nt * 16 + i;
+    return OFF_W2 + ((mt * 16 + m) * 32 + n % 32) * 9 + n / 32;
+  };
+  if (slot < 4) return w2(slot & 1, wave + IW * (slot >> 1));
+  const int id = wave + IW * (slot - 4);
+  if (id < 4) return w2(id & 1, 16 + (id >> 1));
+  if (id < 16) {
+    const int e = id < 10 ? id - 4 : id - 10, c32 = (e & 1) * 16 + m, n = (e >> 1) * 16 + i, tap = n / 4, c4 = n % 4;
+    if (id < 10) return tap < 9 ? OFF_W3 + (c4 * 32 + c32) * 9 + tap : -1;
+    return tap < 9 ? OFF_W1 + (c32 * 4 + c4) * 9 + tap : n == 36 ? OFF_B1 + c32 : -1;
+  }
+  if (id < 18) return i == 0 ? OFF_B2 + (id - 16) * 16 + m : -1;
+  return id == 18 && m == 0 && i < 4 ? OFF_B3 + i : -1;
+}
+
+struct GradSumArgs {
+  const float *rows, *lossp;
+  int nrows;
+  float* out;               // gradients (unless TRAIN) and, behind them, the loss: host memory
+  float *par, *am, *av;
+  float lr, c1, c2;
+  bf16 *W1, *W2, *W3, *T2, *T3;
+};
+
+// Rows of partial sums added in a fixed order: a block takes 64 places of the
+// row and 16 row phases (rows r, r + 16, ..., 16 loads in flight: 256 rows in
+// one memory latency; with 4 phases 6.7 us at 256 rows), then adds the phases
+// in pairs; the last block adds the loss.  Results that the caller waits for
+// go straight to host memory (a copy command cost more than both kernels'
+// launches).  TRAIN: the thread that holds a parameter's gradient takes its
+// Adam step (bias-corrected) and writes the new value into the bf16 matrices.
+template <bool TRAIN>
+__global__ void __launch_bounds__(1024) grad_sum_kernel(const GradSumArgs a) {
+  constexpr int PH = 16, U = 16;
+  __shared__ float red[PH][64];
+  const int t = threadIdx.x & 63, ph = threadIdx.x >> 6;
+  if (blockIdx.x == GRAD_ROW / 64) {
+    if (ph) return;
+    float s = 0.f;
+    for (int r = t; r < a.nrows; r += 64) s += a.lossp[r];
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) s += __shfl_xor(s, o);
+    if (t == 0) a.out[OLB_CLOSURE_NPARAM] = s;
+    return;
+  }
+  const int c = blockIdx.x * 64 + t;
+  const float* src = a.rows + c;
+  float s = 0.f;
+  int r = ph;
+  for (; r + PH * (U - 1) < a.nrows; r += PH * U) {
+    float v[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) v[j] = src[(size_t)(r + PH * j) * GRAD_ROW];
+#pragma unroll
+    for (int j = 0; j < U; ++j) s += v[j];
+  }
+  for (; r < a.nrows; r += PH) s += src[(size_t)r * GRAD_ROW];
+  red[ph][t] = s;
+  __syncthreads();
+  if (ph) return;
+  float half[PH];
+#pragma unroll
+  for (int j = 0; j < PH; ++j) half[j] = red[j][t];
+#pragma unroll
+  for (int w = PH / 2; w > 0; w >>= 1)
+#pragma unroll
+    for (int j = 0; j < w; ++j) half[j] += half[j + w];
+  const float gr = half[0];
+  const int k = grad_param(c);
+  if (k < 0) return;
+  if constexpr (!TRAIN) {
+    a.out[k] = gr;
+  } else {
+    const float mi = ADAM_B1 * a.am[k] + (1.f - ADAM_B1) * gr;
+    const float vi = ADAM_B2 * a.av[k] + (1.f - ADAM_B2) * gr * gr;
+    a.am[k] = mi;
+    a.av[k] = vi;
+    const float w = a.par[k] - a.lr * (mi * a.c1) / (sqrtf(vi * a.c2) + ADAM_EPS);
+    a.par[k] = w;
+    const bf16 b = to_bf16(w);
+    constexpr int KP1 = kp_of(4), KP2 = kp_of(32);
+    if (k < OFF_B1) {
+      const int co = k / 36, ci = k / 9 % 4, tap = k % 9;
+      a.W1[co * KP1 + tap * 4 + ci] = b;
+    } else if (k >= OFF_W2 && k < OFF_B2) {
+      const int q = k - OFF_W2, co = q / 288, ci = q / 9 % 32, tap = q % 9;
+      a.W2[co * KP2 + tap * 32 + ci] = b;
+      a.T2[ci * KP2 + (8 - tap) * 32 + co] = b;
+    } else if (k >= OFF_W3 && k < OFF_B3) {
+      const int q = k - OFF_W3, co = q / 288, ci = q / 9 % 32, tap = q % 9;
+      a.W3[co * KP2 + tap * 32 + ci] = b;
+      a.T3[ci * KP1 + (8 - tap) * 4 + co] = b;
+    }
+  }
+}
+
 // f <- f + f^eq(m') - f^eq(m) with m' = m + dm (absolute == 0) or m' = dm
 // (absolute == 1) where m' is admissible (finite, 0 < n < 1/b, T > 0); other
 // nodes keep f (counted in skipped).
@@ -960,46 +1105,8 @@ static_assert(NPARAM == OLB_CLOSURE_NPARAM, "parameter count");
 constexpr size_t AL = 256;
 size_t al(size_t v) { return (v + AL - 1) / AL * AL; }
 
-// Pixel chunks of the weight-gradient kernel: about 512 workgroups (tile
-// groups x chunks), chunks of a multiple of 16 pixels
-template <int CIN, int COUT>
-struct BwdWeightGrid {
-  static constexpr int tiles = ((COUT + 15) / 16) * (olbk::kp_of(CIN) / 16);
-  static constexpr int groups = (tiles + 3) / 4;
-  int chunk, nchunks;
-  explicit BwdWeightGrid(int P) {
-    const int chunks = std::max(1, std::min((P + 63) / 64, 512 / groups));
-    chunk = ((P + chunks - 1) / chunks + 15) / 16 * 16;
-    nchunks = (P + chunk - 1) / chunk;
-  }
-};
-int bias_blocks(int P) { return std::min(1024, std::max(1, P / 256)); }
-int loss_blocks(int P) { return std::min(1024, (P + 255) / 256); }
-
-// Rows of partial sums of the backward pass, in the order of the parameter
-// vector's blocks: W1, b1, W2, b2, W3, b3, then the loss
-struct GradParts {
-  int rows[7], n[7];
-  size_t off[7], floats;
-  explicit GradParts(int P) {
-    rows[0] = BwdWeightGrid<4, 32>(P).nchunks;
-    rows[2] = BwdWeightGrid<32, 32>(P).nchunks;
-    rows[4] = BwdWeightGrid<32, 4>(P).nchunks;
-    rows[1] = rows[3] = rows[5] = bias_blocks(P);
-    rows[6] = loss_blocks(P);
-    const int ns[7] = {32 * 4 * 9, 32, 32 * 32 * 9, 32, 4 * 32 * 9, 4, 1};
-    floats = 0;
-    for (int k = 0; k < 7; ++k) {
-      n[k] = ns[k];
-      off[k] = floats;
-      floats += (size_t)rows[k] * n[k];
-    }
-  }
-};
-
 struct CLayout {
-  size_t x0, z1, a1, z2, a2, z3, g3, g2, g1, mom, delta, par, grad, am, av, w1, w2, w3, loss, skip, part4, gpart,
-      total;
+  size_t x0, a1, a2, z3, mom, delta, par, am, av, w1, w2, w3, t2, t3, skip, part4, gpart, lossp, total;
 };
 
 CLayout clayout(int nx, int ny) {
@@ -1008,27 +1115,24 @@ CLayout clayout(int nx, int ny) {
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o += al(bytes); return r; };
   L.x0 = take(P * 4 * 2);
-  L.z1 = take(P * 32 * 4);
   L.a1 = take(P * 32 * 2);
-  L.z2 = take(P * 32 * 4);
   L.a2 = take(P * 32 * 2);
   L.z3 = take(P * 4 * 4);
-  L.g3 = take(P * 4 * 2);
-  L.g2 = take(P * 32 * 2);
-  L.g1 = take(P * 32 * 2);
   L.mom = take(P * 4 * 8);
   L.delta = take(P * 4 * 8);
   L.par = take(NPARAM * 4);
-  L.grad = take(NPARAM * 4);
   L.am = take(NPARAM * 4);
   L.av = take(NPARAM * 4);
   L.w1 = take(32 * olbk::kp_of(4) * 2);
   L.w2 = take(32 * olbk::kp_of(32) * 2);
   L.w3 = take(16 * olbk::kp_of(32) * 2);
-  L.loss = take(4);
+  L.t2 = take(32 * olbk::kp_of(32) * 2);
+  L.t3 = take(32 * olbk::kp_of(4) * 2);
   L.skip = take(4);
   L.part4 = take(olbk::MAX_PARTS * 4 * 8);
-  L.gpart = take(GradParts((int)P).floats * 4);
+  const size_t rows = olbk::grad_rows(nx, ny);
+  L.gpart = take(rows * olbk::GRAD_ROW * 4);
+  L.lossp = take(rows * 4);
   L.total = o;
   return L;
 }
@@ -1043,7 +1147,12 @@ struct olb_closure {
   int adam_t = 0;
   int conserve_mask = 7;  // n, u_x, u_y corrections are made mean-free
   bool have_params = false;
+  float* host = nullptr;   // page-locked, NPARAM + 1: gradients and loss
   std::string err;
+
+  ~olb_closure() {
+    if (host) (void)hipHostFree(host);
+  }
 
   template <typename T>
   T* at(size_t off) { return reinterpret_cast<T*>(ws + off); }
@@ -1054,14 +1163,12 @@ struct olb_closure {
     return OLB_E_DEVICE;
   }
 
-  int pix_blocks() const { return (P + 63) / 64; }  // 4 waves x 16 pixels
   // 16-pixel tiles per wave of the forward convolutions: up to FWD_MT while
   // at least 1024 workgroups remain
   int fwd_mtw() const { return std::max(1, std::min(olbk::FWD_MT, P / (64 * 1024))); }
   int fwd_blocks() const { return (P + 64 * fwd_mtw() - 1) / (64 * fwd_mtw()); }
 
-  // keep_z: also store the pre-activations of the hidden layers (backward)
-  olb_status forward(const double* dev_m, bool keep_z) {
+  olb_status forward(const double* dev_m) {
     using namespace olbk;
     const float* par = at<float>(L.par);
     const float* b1 = par + 32 * 4 * 9;
@@ -1070,20 +1177,13 @@ struct olb_closure {
     hipLaunchKernelGGL(prep_kernel, dim3((P + 255) / 256), dim3(256), 0, stream, dev_m, P, norm, at<bf16>(L.x0));
     const dim3 fg(fwd_blocks());
     const int mtw = fwd_mtw();
-    if (keep_z) {
-      hipLaunchKernelGGL((conv_fwd<4, 32, true, true, true>), fg, dim3(256), 0, stream,
-                         at<bf16>(L.x0), at<bf16>(L.w1), b1, at<float>(L.z1), at<bf16>(L.a1), nx, ny, mtw);
-      hipLaunchKernelGGL((conv_fwd<32, 32, true, true, true>), fg, dim3(256), 0, stream,
-                         at<bf16>(L.a1), at<bf16>(L.w2), b2, at<float>(L.z2), at<bf16>(L.a2), nx, ny, mtw);
-    } else {
-      hipLaunchKernelGGL((conv_fwd<4, 32, true, false, true>), fg, dim3(256), 0, stream,
-                         at<bf16>(L.x0), at<bf16>(L.w1), b1, at<float>(L.z1), at<bf16>(L.a1), nx, ny, mtw);
-      hipLaunchKernelGGL((conv_fwd<32, 32, true, false, true>), fg, dim3(256), 0, stream,
-                         at<bf16>(L.a1), at<bf16>(L.w2), b2, at<float>(L.z2), at<bf16>(L.a2), nx, ny, mtw);
-    }
+    hipLaunchKernelGGL((conv_fwd<4, 32, true>), fg, dim3(256), 0, stream, at<bf16>(L.x0), at<bf16>(L.w1), b1,
+                       (float*)nullptr, at<bf16>(L.a1), nx, ny, mtw);
+    hipLaunchKernelGGL((conv_fwd<32, 32, true>), fg, dim3(256), 0, stream, at<bf16>(L.a1), at<bf16>(L.w2), b2,
+                       (float*)nullptr, at<bf16>(L.a2), nx, ny, mtw);
     // layer 3: no activation, only the FP32 output
-    hipLaunchKernelGGL((conv_fwd<32, 4, false, true, false>), fg, dim3(256), 0, stream,
-                       at<bf16>(L.a2), at<bf16>(L.w3), b3, at<float>(L.z3), at<bf16>(L.g3), nx, ny, mtw);
+    hipLaunchKernelGGL((conv_fwd<32, 4, false>), fg, dim3(256), 0, stream, at<bf16>(L.a2), at<bf16>(L.w3), b3,
+                       at<float>(L.z3), (bf16*)nullptr, nx, ny, mtw);
     return hip(hipGetLastError(), "closure forward");
   }
 
@@ -1103,10 +1203,10 @@ struct olb_closure {
     return hip(hipGetLastError(), "closure inference");
   }
 
-  // layer-by-layer forward (the reference for the fused kernel; training)
+  // layer-by-layer forward (the reference for the fused kernels)
   olb_status forward_layers(const double* dev_m, double* dev_delta) {
     using namespace olbk;
-    olb_status s = forward(dev_m, false);
+    olb_status s = forward(dev_m);
     if (s) return s;
     double* part4 = at<double>(L.part4);
     const int nparts = std::min(MAX_PARTS, (P + 255) / 256);
@@ -1117,57 +1217,31 @@ struct olb_closure {
     return hip(hipGetLastError(), "delta kernel");
   }
 
-  // Gradient of the loss for every parameter, and the loss: each kernel
-  // writes partial sums (per pixel chunk or block) to its rows of L.gpart,
-  // which sum_segments then adds in a fixed order into L.grad and L.loss.
-  olb_status backward(const double* dev_m, const double* dev_ref) {
+  // The loss, in host[NPARAM], and with lr == 0 its gradient for every
+  // parameter, in host; with lr > 0 the Adam step of the gradients and the
+  // bf16 matrices of the new parameters.  (Once the stream is waited for.)
+  olb_status backward(const double* dev_m, const double* dev_ref, float lr, float c1, float c2) {
     using namespace olbk;
-    const GradParts gp(P);
-    float* part = at<float>(L.gpart);
-    hipLaunchKernelGGL(loss_kernel, dim3(gp.rows[6]), dim3(256), 0, stream, at<float>(L.z3), dev_m, dev_ref, P,
-                       norm, at<bf16>(L.g3), part + gp.off[6]);
-    // layer 3
-    launch_bwd_weight<32, 4>(at<bf16>(L.g3), at<bf16>(L.a2), part + gp.off[4]);
-    hipLaunchKernelGGL((bias_grad<4>), dim3(gp.rows[5]), dim3(256), 0, stream, at<bf16>(L.g3), part + gp.off[5], P);
-    hipLaunchKernelGGL((conv_bwd_data<32, 4>), dim3(pix_blocks()), dim3(256), 0, stream, at<bf16>(L.g3),
-                       at<bf16>(L.w3), at<float>(L.z2), at<bf16>(L.g2), nx, ny);
-    // layer 2
-    launch_bwd_weight<32, 32>(at<bf16>(L.g2), at<bf16>(L.a1), part + gp.off[2]);
-    hipLaunchKernelGGL((bias_grad<32>), dim3(gp.rows[3]), dim3(256), 0, stream, at<bf16>(L.g2), part + gp.off[3],
-                       P);
-    hipLaunchKernelGGL((conv_bwd_data<32, 32>), dim3(pix_blocks()), dim3(256), 0, stream, at<bf16>(L.g2),
-                       at<bf16>(L.w2), at<float>(L.z1), at<bf16>(L.g1), nx, ny);
-    // layer 1 (the input needs no gradient)
-    launch_bwd_weight<4, 32>(at<bf16>(L.g1), at<bf16>(L.x0), part + gp.off[0]);
-    hipLaunchKernelGGL((bias_grad<32>), dim3(gp.rows[1]), dim3(256), 0, stream, at<bf16>(L.g1), part + gp.off[1],
-                       P);
-    // the parameter vector's blocks follow each other in gp's order
-    SumSegs segs{};
-    float* dst = at<float>(L.grad);
-    int bx = 1;
-    for (int k = 0; k < 7; ++k) {
-      segs.s[k] = SumSeg{part + gp.off[k], k < 6 ? dst : at<float>(L.loss), gp.rows[k], gp.n[k]};
-      if (k < 6) dst += gp.n[k];
-      bx = std::max(bx, (gp.n[k] + 255) / 256);
-    }
-    hipLaunchKernelGGL(sum_segments, dim3(bx, 7), dim3(256), 0, stream, segs);
+    const float* par = at<float>(L.par);
+    const int grid = infer_grid(grad_tiles(nx, ny));
+    GradArgs ga{dev_m, dev_ref, norm, at<bf16>(L.w1), at<bf16>(L.w2), at<bf16>(L.w3), at<bf16>(L.t2), at<bf16>(L.t3),
+                par + 32 * 4 * 9, par + (32 * 4 * 9 + 32) + 32 * 32 * 9, par + (NPARAM - 4), nx, ny,
+                at<float>(L.gpart), at<float>(L.lossp)};
+    hipLaunchKernelGGL(grad_kernel, dim3(grid), dim3(64 * IW), 0, stream, ga);
+    GradSumArgs sa{at<float>(L.gpart), at<float>(L.lossp), grid, host, at<float>(L.par),
+                   at<float>(L.am), at<float>(L.av), lr, c1, c2,
+                   at<bf16>(L.w1), at<bf16>(L.w2), at<bf16>(L.w3), at<bf16>(L.t2), at<bf16>(L.t3)};
+    if (lr > 0.f)
+      hipLaunchKernelGGL(grad_sum_kernel<true>, dim3(GRAD_ROW / 64 + 1), dim3(1024), 0, stream, sa);
+    else
+      hipLaunchKernelGGL(grad_sum_kernel<false>, dim3(GRAD_ROW / 64 + 1), dim3(1024), 0, stream, sa);
     return hip(hipGetLastError(), "closure backward");
-  }
-
-  // about 512 workgroups per weight gradient: tile groups x pixel chunks;
-  // dWp receives one row of partial sums per chunk
-  template <int CIN, int COUT>
-  void launch_bwd_weight(const olbk::bf16* G, const olbk::bf16* X, float* dWp) {
-    const BwdWeightGrid<CIN, COUT> g(P);
-    hipLaunchKernelGGL((olbk::conv_bwd_weight<CIN, COUT>), dim3(BwdWeightGrid<CIN, COUT>::groups, g.nchunks),
-                       dim3(256), 0, stream, G, X, dWp, nx, ny, g.chunk);
   }
 
   olb_status pack() {
     using namespace olbk;
-    const int n = 32 * kp_of(4) + 32 * kp_of(32) + 16 * kp_of(32);
-    hipLaunchKernelGGL(pack_weights, dim3((n + 255) / 256), dim3(256), 0, stream, at<float>(L.par),
-                       at<bf16>(L.w1), at<bf16>(L.w2), at<bf16>(L.w3));
+    hipLaunchKernelGGL(pack_weights, dim3((PACK_ALL + 255) / 256), dim3(256), 0, stream, at<float>(L.par),
+                       at<bf16>(L.w1), at<bf16>(L.w2), at<bf16>(L.w3), at<bf16>(L.t2), at<bf16>(L.t3));
     return hip(hipGetLastError(), "weight pack");
   }
 };
@@ -1203,7 +1277,11 @@ olb_status olb_closure_init(int32_t nx, int32_t ny, void* dev_workspace, size_t 
     c->norm.in_inv_scale[k] = 1.f;
     c->norm.out_scale[k] = 1.f;
   }
-  olb_status s = c->hip(hipMemsetAsync(c->ws, 0, L.total, c->stream), "workspace clear");
+  // parameters and Adam state start at zero; every other part of the workspace
+  // is written before it is read
+  olb_status s = c->hip(hipHostMalloc(reinterpret_cast<void**>(&c->host), (NPARAM + 1) * 4, hipHostMallocDefault),
+                        "host buffer");
+  if (!s) s = c->hip(hipMemsetAsync(c->ws + L.par, 0, L.w1 - L.par, c->stream), "workspace clear");
   if (!s) s = c->hip(hipStreamSynchronize(c->stream), "stream sync");
   if (s) {
     delete c;
@@ -1271,35 +1349,27 @@ olb_status olb_closure_gradients(olb_closure* c, const double* dev_moments, cons
                                  float* grad, float* loss) {
   if (!c || !dev_moments || !dev_reference || !grad) return OLB_E_ARG;
   if (!c->have_params) return OLB_E_STATE;
-  olb_status s = c->forward(dev_moments, true);
-  if (!s) s = c->backward(dev_moments, dev_reference);
-  if (!s) s = c->hip(hipMemcpyAsync(grad, c->at<float>(c->L.grad), NPARAM * 4, hipMemcpyDeviceToHost,
-                                    c->stream), "grad download");
-  if (!s && loss)
-    s = c->hip(hipMemcpyAsync(loss, c->at<float>(c->L.loss), 4, hipMemcpyDeviceToHost, c->stream), "loss");
+  olb_status s = c->backward(dev_moments, dev_reference, 0.f, 0.f, 0.f);
   if (!s) s = c->hip(hipStreamSynchronize(c->stream), "stream sync");
-  return s;
+  if (s) return s;
+  std::memcpy(grad, c->host, NPARAM * 4);
+  if (loss) *loss = c->host[NPARAM];
+  return OLB_OK;
 }
 
 olb_status olb_closure_train_step(olb_closure* c, const double* dev_moments, const double* dev_reference,
                                   float lr, float* loss) {
   if (!c || !dev_moments || !dev_reference || !(lr > 0.f)) return OLB_E_ARG;
   if (!c->have_params) return OLB_E_STATE;
-  olb_status s = c->forward(dev_moments, true);
-  if (!s) s = c->backward(dev_moments, dev_reference);
+  const int t = c->adam_t + 1;
+  const float c1 = 1.0f / (1.0f - std::pow(olbk::ADAM_B1, (float)t));
+  const float c2 = 1.0f / (1.0f - std::pow(olbk::ADAM_B2, (float)t));
+  olb_status s = c->backward(dev_moments, dev_reference, lr, c1, c2);
   if (s) return s;
-  c->adam_t += 1;
-  const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-  const float c1 = 1.0f / (1.0f - std::pow(b1, (float)c->adam_t));
-  const float c2 = 1.0f / (1.0f - std::pow(b2, (float)c->adam_t));
-  hipLaunchKernelGGL(olbk::adam_kernel, dim3((NPARAM + 255) / 256), dim3(256), 0, c->stream,
-                     c->at<float>(c->L.par), c->at<float>(c->L.grad), c->at<float>(c->L.am),
-                     c->at<float>(c->L.av), NPARAM, lr, b1, b2, eps, c1, c2);
-  s = c->hip(hipGetLastError(), "adam kernel");
-  if (!s) s = c->pack();
-  if (!s && loss) {
-    s = c->hip(hipMemcpyAsync(loss, c->at<float>(c->L.loss), 4, hipMemcpyDeviceToHost, c->stream), "loss");
-    if (!s) s = c->hip(hipStreamSynchronize(c->stream), "stream sync");
+  c->adam_t = t;
+  if (loss) {
+    s = c->hip(hipStreamSynchronize(c->stream), "stream sync");
+    if (!s) *loss = c->host[NPARAM];
   }
   return s;
 }
@@ -1428,8 +1498,8 @@ olb_status olb_closure_forward_noalloc(int32_t nx, int32_t ny, const float* dev_
   bf16* W3 = reinterpret_cast<bf16*>(sc + NA_W3);
   double* part4 = conserve_mask ? reinterpret_cast<double*>(sc + NA_PART) : nullptr;
   hipStream_t st = (hipStream_t)hip_stream;
-  const int n = 32 * kp_of(4) + 32 * kp_of(32) + 16 * kp_of(32);
-  hipLaunchKernelGGL(pack_weights, dim3((n + 255) / 256), dim3(256), 0, st, dev_params, W1, W2, W3);
+  hipLaunchKernelGGL(pack_weights, dim3((PACK_FORWARD + 255) / 256), dim3(256), 0, st, dev_params, W1, W2, W3,
+                     (bf16*)nullptr, (bf16*)nullptr);
   const int tiles_x = (nx + FT - 1) / FT, tiles_y = (ny + FT - 1) / FT, ntiles = tiles_x * tiles_y;
   const int P = nx * ny;
   const int grid = infer_grid(ntiles);

@@ -1,7 +1,8 @@
 """Small lattices: the kernels that update them (16 x 8 tiles split by
 velocity rows, wall ghosts formed in the tile; whole steps in one workgroup
 for lattices of up to 192 nodes) against the stage kernel, which a chosen
-tile height selects.  Every node's sums are taken in the same
+tile height selects.  And the closure's gradients on small and ragged
+lattices.  Every node's sums are taken in the same
 order by both, so f, the moments and the wall densities agree to the bit."""
 import numpy as np
 import pytest
@@ -134,3 +135,42 @@ def test_resident_batch_steps_and_graphs(kind):
     for other in got[1:]:
         for u, v in zip(got[0], other):
             np.testing.assert_array_equal(u, v)
+
+
+@pytest.mark.parametrize("shape", [(5, 3), (8, 8), (9, 17), (130, 24), (7, 300), (300, 260)],
+                         ids=lambda v: f"{v[0]}x{v[1]}")
+def test_closure_gradients_at_tile_edges(shape):
+    """The fused gradient kernel on lattices smaller than its 8 x 8 tile's
+    halo, exact and ragged tiles, and more tiles than workgroups, against the
+    oracle with the kernels' bf16 roundings.  What is left is FP32 summation
+    order, which moves a bf16 rounding (2^-8) of one activation or gradient in
+    some thousands: well below 5e-3 of a block's norm."""
+    import torch
+    from oracle import cnn
+    olb = _olb()
+    nx, ny = shape
+    params = I.closure_params(seed=7)
+    m = I.closure_moments(nx, ny, seed=21)
+    norm = (m.mean(axis=(1, 2)), np.maximum(m.std(axis=(1, 2)), 1e-3), np.array([1e-3, 2e-4, 2e-4, 1e-4]))
+    U = 2.0 * I.uniform(22, 4 * nx * ny).reshape(4, ny, nx) - 1.0
+    ref = m + U * norm[2][:, None, None]
+    c = olb.Closure(nx, ny)
+    assert not c.get_params().any()          # zero until set
+    c.set_norm(*norm)
+    c.set_params(params)
+    dev = lambda a: torch.tensor(a, dtype=torch.float64, device="cuda:0").contiguous()
+    g, loss = c.gradients(dev(m), dev(ref))
+    want_loss, want = cnn.loss_and_gradient(params, m, ref, norm, bf16_mirror=True)
+    print(f"[closure] gradients {nx}x{ny}: loss {loss:.6e} oracle {want_loss:.6e}", flush=True)
+    assert abs(loss - want_loss) <= 1e-4 * want_loss
+    o = 0
+    for name, block in cnn.BLOCKS:
+        k = int(np.prod(block))
+        e = np.linalg.norm(g[o:o + k] - want[o:o + k]) / np.linalg.norm(want[o:o + k])
+        assert e < 5e-3, (name, e)
+        o += k
+    # a training step reports the same loss and steps along the same gradient
+    assert c.train_step(dev(m), dev(ref), 1e-3) == loss
+    step = (params - c.get_params()) / 1e-3
+    far = np.abs(g) > 1e-3 * np.abs(g).max()
+    np.testing.assert_allclose(step[far], np.sign(g[far]), atol=2e-3)

@@ -958,7 +958,8 @@ __device__ __forceinline__ int grad_param(int c) {
 struct GradSumArgs {
   const float *rows, *lossp;
   int nrows;
-  float* out;               // gradients (unless TRAIN) and, behind them, the loss: host memory
+  float* out;               // gradients (unless TRAIN) and, behind them, the loss: host memory; nullptr if the
+                            // caller does not wait, who may free the object before this runs
   float *par, *am, *av;
   float lr, c1, c2;
   bf16 *W1, *W2, *W3, *T2, *T3;
@@ -977,7 +978,7 @@ __global__ void __launch_bounds__(1024) grad_sum_kernel(const GradSumArgs a) {
   __shared__ float red[PH][64];
   const int t = threadIdx.x & 63, ph = threadIdx.x >> 6;
   if (blockIdx.x == GRAD_ROW / 64) {
-    if (ph) return;
+    if (ph || !a.out) return;
     float s = 0.f;
     for (int r = t; r < a.nrows; r += 64) s += a.lossp[r];
 #pragma unroll
@@ -1217,10 +1218,11 @@ struct olb_closure {
     return hip(hipGetLastError(), "delta kernel");
   }
 
-  // The loss, in host[NPARAM], and with lr == 0 its gradient for every
-  // parameter, in host; with lr > 0 the Adam step of the gradients and the
-  // bf16 matrices of the new parameters.  (Once the stream is waited for.)
-  olb_status backward(const double* dev_m, const double* dev_ref, float lr, float c1, float c2) {
+  // The loss, in host[NPARAM] if want_loss, and with lr == 0 its gradient for
+  // every parameter, in host; with lr > 0 the Adam step of the gradients and
+  // the bf16 matrices of the new parameters.  Nothing writes to host unless
+  // the caller waits for the stream: lr == 0 or want_loss.
+  olb_status backward(const double* dev_m, const double* dev_ref, float lr, float c1, float c2, bool want_loss) {
     using namespace olbk;
     const float* par = at<float>(L.par);
     const int grid = infer_grid(grad_tiles(nx, ny));
@@ -1228,7 +1230,7 @@ struct olb_closure {
                 par + 32 * 4 * 9, par + (32 * 4 * 9 + 32) + 32 * 32 * 9, par + (NPARAM - 4), nx, ny,
                 at<float>(L.gpart), at<float>(L.lossp)};
     hipLaunchKernelGGL(grad_kernel, dim3(grid), dim3(64 * IW), 0, stream, ga);
-    GradSumArgs sa{at<float>(L.gpart), at<float>(L.lossp), grid, host, at<float>(L.par),
+    GradSumArgs sa{at<float>(L.gpart), at<float>(L.lossp), grid, want_loss ? host : nullptr, at<float>(L.par),
                    at<float>(L.am), at<float>(L.av), lr, c1, c2,
                    at<bf16>(L.w1), at<bf16>(L.w2), at<bf16>(L.w3), at<bf16>(L.t2), at<bf16>(L.t3)};
     if (lr > 0.f)
@@ -1349,7 +1351,7 @@ olb_status olb_closure_gradients(olb_closure* c, const double* dev_moments, cons
                                  float* grad, float* loss) {
   if (!c || !dev_moments || !dev_reference || !grad) return OLB_E_ARG;
   if (!c->have_params) return OLB_E_STATE;
-  olb_status s = c->backward(dev_moments, dev_reference, 0.f, 0.f, 0.f);
+  olb_status s = c->backward(dev_moments, dev_reference, 0.f, 0.f, 0.f, true);
   if (!s) s = c->hip(hipStreamSynchronize(c->stream), "stream sync");
   if (s) return s;
   std::memcpy(grad, c->host, NPARAM * 4);
@@ -1364,7 +1366,7 @@ olb_status olb_closure_train_step(olb_closure* c, const double* dev_moments, con
   const int t = c->adam_t + 1;
   const float c1 = 1.0f / (1.0f - std::pow(olbk::ADAM_B1, (float)t));
   const float c2 = 1.0f / (1.0f - std::pow(olbk::ADAM_B2, (float)t));
-  olb_status s = c->backward(dev_moments, dev_reference, lr, c1, c2);
+  olb_status s = c->backward(dev_moments, dev_reference, lr, c1, c2, loss != nullptr);
   if (s) return s;
   c->adam_t = t;
   if (loss) {

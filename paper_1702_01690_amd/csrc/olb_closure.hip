@@ -209,21 +209,27 @@ __global__ void __launch_bounds__(256) conv_fwd(const bf16* __restrict__ X, cons
 // infer_kernel)
 constexpr int MAX_PARTS = 256;
 
-// Fixed-order total of nparts <= MAX_PARTS rows of four FP64 partial sums,
-// for a block of 256 threads: thread t loads row t, then a tree over the
-// threads.  Every block (and every run) gets the same bits; red[c][0] holds
-// channel c's total on return.  All threads of the block must call it.
-__device__ __forceinline__ void block_total4(const double* __restrict__ part, int nparts, double (*red)[256]) {
+// Fixed-order total of nparts rows of four FP64 partial sums, for a block of
+// 256 threads: thread t adds channel t % 4 of rows t / 4, t / 4 + 64, ... (a
+// row is 32 consecutive bytes, all of a thread's loads in flight), the wave
+// folds its 16 rows, then the four waves' totals are added.  Every block (and
+// every run) gets the same bits; red[0][c] holds channel c's total on return.
+// All threads of the block must call it.  (A row of four per thread and eight
+// barriers of a tree took 1 us more.)
+__device__ __forceinline__ void block_total4(const double* __restrict__ part, int nparts, double (*red)[4]) {
+  constexpr int U = MAX_PARTS / 64;
   const int t = threadIdx.x;
+  double v[U], s = 0.0;
 #pragma unroll
-  for (int c = 0; c < 4; ++c) red[c][t] = t < nparts ? part[(size_t)t * 4 + c] : 0.0;
+  for (int j = 0; j < U; ++j) v[j] = t + j * 256 < nparts * 4 ? part[t + j * 256] : 0.0;
+#pragma unroll
+  for (int j = 0; j < U; ++j) s += v[j];
+#pragma unroll
+  for (int o = 4; o < 64; o <<= 1) s += __shfl_xor(s, o);
+  if ((t & 63) < 4) red[t >> 6][t & 3] = s;
   __syncthreads();
-  for (int h = 128; h > 0; h >>= 1) {
-    if (t < h)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) red[c][t] += red[c][t + h];
-    __syncthreads();
-  }
+  if (t < 4) red[0][t] = (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
+  __syncthreads();
 }
 
 // ------------------------------------------------------------ glue kernels --
@@ -342,13 +348,13 @@ __global__ void __launch_bounds__(256) output_sums(const float* __restrict__ Z3,
 __global__ void __launch_bounds__(256) delta_kernel(const float* __restrict__ Z3, int P, Norm nm,
                                                     const double* __restrict__ part4, int nparts,
                                                     int conserve_mask, double* __restrict__ delta) {
-  __shared__ double red[4][256];
+  __shared__ double red[4][4];
   if (conserve_mask) block_total4(part4, nparts, red);
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= P) return;
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    const double mean = ((conserve_mask >> c) & 1) ? red[c][0] / (double)P : 0.0;
+    const double mean = ((conserve_mask >> c) & 1) ? red[0][c] / (double)P : 0.0;
     delta[(size_t)c * P + p] = ((double)Z3[(size_t)p * 4 + c] - mean) * (double)nm.out_scale[c];
   }
 }
@@ -659,17 +665,50 @@ static int infer_grid(int ntiles) {
 
 // delta[c] -= mean_c * out_scale[c] for the channels in mask; the channel
 // totals of the normalised output over P nodes are the nparts rows of
-// partial sums of infer_kernel, totalled in a fixed order; 256 threads per
-// block
+// partial sums of infer_kernel, totalled in a fixed order by every block while
+// its first corrections are on their way.
+template <int J>
 __global__ void __launch_bounds__(256) project_kernel(double* __restrict__ delta, int P, Norm nm,
                                                       const double* __restrict__ part4, int nparts, int mask) {
-  __shared__ double red[4][256];
-  block_total4(part4, nparts, red);
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= P) return;
+  __shared__ double red[4][4];
+  double v[4][J];
+  auto load = [&](int p0) {
 #pragma unroll
-  for (int c = 0; c < 4; ++c)
-    if ((mask >> c) & 1) delta[(size_t)c * P + p] -= red[c][0] / (double)P * (double)nm.out_scale[c];
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const int p = p0 + j * 256;
+        v[c][j] = p < P && ((mask >> c) & 1) ? delta[(size_t)c * P + p] : 0.0;
+      }
+  };
+  int p0 = blockIdx.x * (256 * J) + threadIdx.x;
+  load(p0);
+  block_total4(part4, nparts, red);
+  double shift[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) shift[c] = red[0][c] / (double)P * (double)nm.out_scale[c];
+  while (p0 < P) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const int p = p0 + j * 256;
+        if (p < P && ((mask >> c) & 1)) delta[(size_t)c * P + p] = v[c][j] - shift[c];
+      }
+    p0 += gridDim.x * (256 * J);
+    load(p0);
+  }
+}
+// A node per thread up to 1024 blocks (four per CU): the shortest chain, 128^2
+// 4.1 us against 5.0 with four.  Beyond that four nodes per thread, whose loads
+// are in flight together, and still at most 1024 blocks, as each totals the
+// partial sums: 2048^2 33 us (one node per thread and a block for each 256 nodes: 41).
+static void launch_project(hipStream_t st, double* delta, int P, const Norm& nm, const double* part4, int nparts, int mask) {
+  if (P <= 256 * 1024)
+    hipLaunchKernelGGL(project_kernel<1>, dim3((P + 255) / 256), dim3(256), 0, st, delta, P, nm, part4, nparts, mask);
+  else
+    hipLaunchKernelGGL(project_kernel<4>, dim3(std::min((P + 1023) / 1024, 1024)), dim3(256), 0, st, delta, P, nm,
+                       part4, nparts, mask);
 }
 
 // ------------------------------------------------------------- gradients --
@@ -1199,8 +1238,7 @@ struct olb_closure {
                        at<bf16>(L.w2), at<bf16>(L.w3), par + 32 * 4 * 9, par + (32 * 4 * 9 + 32) + 32 * 32 * 9,
                        par + (NPARAM - 4), nx, ny, tiles_x, ntiles, dev_delta, part4);
     if (part4)
-      hipLaunchKernelGGL(project_kernel, dim3((P + 255) / 256), dim3(256), 0, stream, dev_delta, P, norm, part4,
-                         grid, conserve_mask);
+      launch_project(stream, dev_delta, P, norm, part4, grid, conserve_mask);
     return hip(hipGetLastError(), "closure inference");
   }
 
@@ -1509,8 +1547,7 @@ olb_status olb_closure_forward_noalloc(int32_t nx, int32_t ny, const float* dev_
                      dev_params + 32 * 4 * 9, dev_params + (32 * 4 * 9 + 32) + 32 * 32 * 9, dev_params + (NPARAM - 4),
                      nx, ny, tiles_x, ntiles, dev_delta, part4);
   if (part4)
-    hipLaunchKernelGGL(project_kernel, dim3((P + 255) / 256), dim3(256), 0, st, dev_delta, P, nm, part4, grid,
-                       conserve_mask);
+    launch_project(st, dev_delta, P, nm, part4, grid, conserve_mask);
   return hipGetLastError() == hipSuccess ? OLB_OK : OLB_E_DEVICE;
 }
 

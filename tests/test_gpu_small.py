@@ -174,3 +174,22 @@ def test_closure_gradients_at_tile_edges(shape):
     step = (params - c.get_params()) / 1e-3
     far = np.abs(g) > 1e-3 * np.abs(g).max()
     np.testing.assert_allclose(step[far], np.sign(g[far]), atol=2e-3)
+
+
+@pytest.mark.parametrize("factor", [2, 3, 4, 8])
+@pytest.mark.parametrize("cells", [(1, 1), (65, 3)], ids=lambda v: f"{v[0]}x{v[1]}")
+def test_restriction_factors(factor, cells):
+    """Every factor with loads of its own and the general one, with rows that
+    start on odd multiples of 8 bytes, against the oracle: sums of r^2 terms
+    and a handful of roundings after them, each 2^-53 of the largest value."""
+    import torch
+    from oracle import cnn
+    olb = _olb()
+    nx, ny = factor * cells[0], factor * cells[1]
+    m = I.closure_moments(nx, ny, seed=31, amplitude=0.05)
+    buf = torch.zeros(4 * nx * ny + 1, dtype=torch.float64, device="cuda:0")
+    fine = buf[1:]                            # 8 bytes past an aligned start
+    fine.copy_(torch.tensor(m.ravel(), dtype=torch.float64))
+    got = olb.restrict(fine, nx, ny, factor).cpu().numpy().reshape(4, cells[1], cells[0])
+    want = cnn.restrict(m, factor)
+    np.testing.assert_allclose(got, want, rtol=0, atol=(factor * factor + 16) * 2.0 ** -53 * 8 * np.abs(m).max())

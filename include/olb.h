@@ -144,8 +144,9 @@ olb_status olb_wall_density(olb_ctx* c, double* nw_lo, double* nw_hi);
 /* Block height of the stage kernel: 8 (default) or 16 waves per workgroup,
  * or 12 with FP32 storage (OLB_E_ARG otherwise); each workgroup updates
  * 63 x by nodes.  Lattices and batches too small to fill the GPU with such
- * tiles take a kernel with 16 x 8 tiles instead, unless this call has chosen
- * a height.  Results do not depend on either (bitwise). */
+ * tiles take a kernel with 16 x 8 tiles instead, and those of which 64 x 8
+ * tiles put fewer on a compute unit one with these, unless this call has
+ * chosen a height.  Results do not depend on either (bitwise). */
 olb_status olb_set_tile(olb_ctx* c, int32_t by);
 /* FP32 departure storage keeps f - rho_ref b_kx b_ky, with the per-axis base
  * b = w (1 + h(0, T - 1)) of the equilibrium at rest and temperature T

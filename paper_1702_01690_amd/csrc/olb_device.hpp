@@ -76,6 +76,7 @@ struct WallBatchArgs {
 // Tile geometry of the stage kernel: 64 lanes across x produce 63 cells, BY
 // waves across y produce BY rows.
 constexpr int TILE_X = 63;
+constexpr int WIDE_X = 64;   // of the wide stage kernel (8 rows)
 // Tiles of the split stage kernel (olb_split.hpp).
 constexpr int SPLIT_X = 16, SPLIT_Y = 8;
 // Lattices that a workgroup of the resident kernel holds whole: up to 64 NG
@@ -86,6 +87,7 @@ constexpr int resident_places(int ng) { return 64 * ng + 16; }
 // One workgroup per tile of the batch's tile queue.
 hipError_t launch_stage(const BatchArgs& a, int real_bytes, int by, bool walls, bool xspec, hipStream_t s);
 // The same with 16 x 8 tiles, wall ghosts included (no launch_walls).
+hipError_t launch_wide(const BatchArgs& a, int real_bytes, bool walls, hipStream_t s);
 hipError_t launch_split(const BatchArgs& a, int real_bytes, bool walls, bool xspec, hipStream_t s);
 // nsteps whole RK-3 steps of every instance, each in one workgroup (every
 // lattice fits ng; a.stage, a.A, a.B and the tiles are unused).

@@ -4,7 +4,7 @@
 // stage_kernel  one RK-3 stage, fused: moments, EOS, 49-point force, Hermite
 //               equilibrium, force term, BGK, WENO-5 fluxes in x and y and the
 //               RK combine, plus the carried (n, Delta p) of the result for the
-//               next stage's stencils.
+//               next stage's stencils; wide_stage_kernel the same in wider tiles.
 // walls_kernel  ghost rows of the stage's source array across y: diffuse-
 //               reflection walls, or a specular plane at the low end.
 // init / moments / carry / pack / unpack  set-up and read-out.
@@ -90,6 +90,17 @@ __device__ __forceinline__ double lane_next(double v) {
   const long long b = __double_as_longlong(v);
   const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x130, 0xf, 0xf, true);
   const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x130, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+// The same with a value of its own for lane 63.
+__device__ __forceinline__ float lane_next(float v, float last) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(last), __float_as_int(v), 0x130, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double lane_next(double v, double last) {
+  const long long b = __double_as_longlong(v), o = __double_as_longlong(last);
+  const int lo = __builtin_amdgcn_update_dpp((int)o, (int)b, 0x130, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp((int)(o >> 32), (int)(b >> 32), 0x130, 0xf, 0xf, false);
   return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
@@ -345,10 +356,11 @@ constexpr int pop_group() { return std::is_same<Real, float>::value ? OLB_GROUP3
 template <typename Real, int BY, bool XSPEC>
 constexpr bool wide_lds() { return std::is_same<Real, float>::value && !XSPEC && BY != 12; }
 
-template <typename Real, int BY, bool WIDE_>
+// TX: cells of a tile row, 63 or 64
+template <typename Real, int BY, bool WIDE_, int TX>
 struct StageLds {
   static constexpr bool WIDE = WIDE_;
-  static constexpr int TW = 69;          // tile columns x0-3 .. x0+65
+  static constexpr int TW = TX + 6;      // tile columns x0-3 .. x0+TX+2
   static constexpr int TH = BY + 6;      // tile rows    y0-3 .. y0+BY+2
   static constexpr int TN = TW * TH;     // values per plane
   static constexpr int G = pop_group<Real>();
@@ -362,8 +374,11 @@ struct StageLds {
   // double-buffered rows of lower-face reconstructions, one per plane buffer
   // (row BY: the tile's top face)
   Real fy[2 * G][BY + 1][64];
-  // x advection of the first group, parked while the force is computed
+  // x advection of the first group, parked while the force is computed (TX =
+  // 64: its left x faces)
   Real ga[G][BY][64];
+  // TX = 64: the right x face of each row's last cell, one row per plane buffer
+  Real fx[2 * G][TX == WIDE_X ? BY : 1];
 };
 
 // FP32 storage: the equilibrium's departure from w rho0 (collision
@@ -425,13 +440,13 @@ constexpr int prefetch_depth() {
   return std::is_same<Real, float>::value ? OLB_PREFETCH32 : OLB_PREFETCH64 - (XSPEC ? 1 : 0);
 }
 
-template <typename Real, int BY, bool WALLS, bool FN, bool XSPEC>
+template <typename Real, int BY, bool WALLS, bool FN, bool XSPEC, int TX>
 __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, const int y0,
-                                           StageLds<Real, BY, wide_lds<Real, BY, XSPEC>()>& sm) {
+                                           StageLds<Real, BY, wide_lds<Real, BY, XSPEC>(), TX>& sm) {
   constexpr bool F32 = std::is_same<Real, float>::value;
-  using SL = StageLds<Real, BY, wide_lds<Real, BY, XSPEC>()>;
+  constexpr bool LAST = TX == WIDE_X;   // the right x face of a row's last cell is computed apart
+  using SL = StageLds<Real, BY, wide_lds<Real, BY, XSPEC>(), TX>;
   constexpr int TW = SL::TW;
-  constexpr int TH = SL::TH;
   constexpr int TN = SL::TN;
   constexpr int PO = SL::PO;
   constexpr int PR = SL::PR;
@@ -451,7 +466,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
   const int nx = a.g.nx, ny = a.g.ny;
   const int64_t ps = a.g.ps;
   const int x = x0 + tx, y = y0 + ty;
-  const bool active = (tx < TILE_X) && (x < nx) && (y < ny);
+  const bool active = (tx < TX) && (x < nx) && (y < ny);
 
   // storage offsets of this thread's tile slots (same for every population)
   // XSPEC: specular planes at both ends of x (Sec. 3.4.1 across x): a halo
@@ -589,7 +604,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
   // WENO face reconstructions of population slot t from its plane: the left
   // x face (its right neighbour's arrives by a lane shift) and the lower y
   // face (published in fy_sh for the wave below); returns the x advection
-  // difference, the lower-face value and the node's own value
+  // difference (LAST: the left x face, for finish), the lower-face value and
+  // the node's own value
   auto faces = [&](int t, Real& advx, Real& ryl, Real& fk) {
     const int k = tile_pop(t);
     const int kx = k % 5, ky = k / 5;
@@ -609,6 +625,18 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
       fy_sh[t % NB][BY][tx] = py > 0.0 ? wrec(d0, d1, d2, d3, d4) : wrec(d5, d4, d3, d2, d1);
       __builtin_amdgcn_sched_barrier(0);
     }
+    // LAST: the right x faces of the rows' last cells, a lane per row, by the
+    // wave half a tile away from the one above
+    if (LAST && kx != 2 && ty == (t + BY / 2) % BY) {
+      __builtin_amdgcn_s_setprio(2);
+      __builtin_amdgcn_sched_barrier(0);
+      const int ct = (min(tx, BY - 1) + 3) * PR + TX;
+      const Real d0 = P[ct], d1 = P[ct + 1], d2 = P[ct + 2], d3 = P[ct + 3], d4 = P[ct + 4], d5 = P[ct + 5];
+      const Real r = px > 0.0 ? wrec(d0, d1, d2, d3, d4) : wrec(d5, d4, d3, d2, d1);
+      if (tx < BY) sm.fx[t % NB][tx] = r;
+      __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     fk = P[ownc];
     Real rxl = 0;
     ryl = 0;
@@ -624,8 +652,12 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
       fy_sh[t % NB][ty][tx] = ryl;
     }
     if (ky != 2 && ty == t % BY) __builtin_amdgcn_s_setprio(0);
-    const Real rxr = (kx != 2) ? lane_next(rxl) : (Real)0;
-    advx = (kx != 2) ? (Real)px * (rxr - rxl) : (Real)0;
+    if (LAST) {
+      advx = rxl;
+    } else {
+      const Real rxr = (kx != 2) ? lane_next(rxl) : (Real)0;
+      advx = (kx != 2) ? (Real)px * (rxr - rxl) : (Real)0;
+    }
   };
 
   // the first group, before the force is known; its x advection waits in
@@ -675,7 +707,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
   // keep the compiler from issuing all ~100 LDS reads at once).
   double Fx, Fy;
   {
-    const int ctx = tx < TILE_X ? tx : TILE_X - 1;
+    const int ctx = tx < TX ? tx : TX - 1;
     const int c = (ty + 3) * TW + (ctx + 3);
     double gxs = 0.0, gys = 0.0, lxs = 0.0, lys = 0.0;
 #pragma unroll
@@ -746,14 +778,18 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int x0, con
     }
   };
 
-  // y-advection of group tg once the upper faces (written by the next wave)
-  // are visible
+  // y-advection (LAST: and x-advection) of group tg once the upper faces
+  // (written by the next wave) are visible
   auto finish_y = [&](int tg, const Real* advx, const Real* ryl) {
 #pragma unroll
     for (int j = 0; j < G; ++j) {
       const int t = tg + j, k = tile_pop(t);
       const int ky = k / 5;
       Real adv = advx[j];
+      if (LAST) {
+        const int kx = k % 5;
+        adv = kx != 2 ? (Real)Rk[kx] * (lane_next(advx[j], sm.fx[t % NB][ty]) - advx[j]) : (Real)0;
+      }
       if (ky != 2) {
         const Real ryt = fy_sh[t % NB][ty + 1][tx];
         adv = fmadd((Real)Rk[ky], ryt - ryl[j], adv);
@@ -892,9 +928,9 @@ __device__ __forceinline__ StageArgs stage_args(const BatchArgs& ba, const InstD
 // 0): an XCD then runs vertically adjacent tiles close together in time, so
 // the halo rows they share are still in its L2 (in row order a tile's lower
 // neighbour starts about half a tile lifetime later and misses them).
-template <typename Real, int BY, bool WALLS, bool FN, bool XSPEC>
-__global__ void __launch_bounds__(64 * BY, min_waves_per_simd<Real>()) stage_kernel(const BatchArgs ba) {
-  __shared__ StageLds<Real, BY, wide_lds<Real, BY, XSPEC>()> sm;
+template <typename Real, int BY, bool WALLS, bool FN, bool XSPEC, int TX>
+__device__ __forceinline__ void stage_queue(const BatchArgs& ba,
+                                            StageLds<Real, BY, wide_lds<Real, BY, XSPEC>(), TX>& sm) {
   const int bid = blockIdx.x;
   const int q8 = ba.total_tiles >> 3, r8 = ba.total_tiles & 7, xcd = bid & 7;
   const int t = xcd * q8 + (xcd < r8 ? xcd : r8) + (bid >> 3);
@@ -918,7 +954,26 @@ __global__ void __launch_bounds__(64 * BY, min_waves_per_simd<Real>()) stage_ker
     tile_y = local / d.tiles_x;
     tile_x = local - tile_y * d.tiles_x;
   }
-  stage_tile<Real, BY, WALLS, FN, XSPEC>(a, tile_x * TILE_X, tile_y * BY, sm);
+  stage_tile<Real, BY, WALLS, FN, XSPEC, TX>(a, tile_x * TX, tile_y * BY, sm);
+}
+
+template <typename Real, int BY, bool WALLS, bool FN, bool XSPEC>
+__global__ void __launch_bounds__(64 * BY, min_waves_per_simd<Real>()) stage_kernel(const BatchArgs ba) {
+  __shared__ StageLds<Real, BY, wide_lds<Real, BY, XSPEC>(), TILE_X> sm;
+  stage_queue<Real, BY, WALLS, FN, XSPEC, TILE_X>(ba, sm);
+}
+
+// The same with tiles of 64 x 8 cells: a lattice 64 k wide takes k tile columns
+// instead of k + 1, and 512^2 two tiles on every CU where 63 x 8 puts three on
+// some (50.6 -> 41.2 us a stage in FP64, 33.3 -> 28.5 in FP32; VALU issue bound
+// as the other).  The 64th cell's right x face has no lane of its own; for each
+// population one wave takes those of the tile's rows (8 of its 64 lanes: 18
+// reconstructions per population and tile instead of 17), and the x advection
+// waits for them until the barrier.
+template <typename Real, bool WALLS, bool FN>
+__global__ void __launch_bounds__(64 * 8, min_waves_per_simd<Real>()) wide_stage_kernel(const BatchArgs ba) {
+  __shared__ StageLds<Real, 8, wide_lds<Real, 8, false>(), WIDE_X> sm;
+  stage_queue<Real, 8, WALLS, FN, false, WIDE_X>(ba, sm);
 }
 
 // Quadratic extrapolation through a wall from the three interior rows next to
@@ -1150,6 +1205,26 @@ hipError_t launch_stage(const BatchArgs& a, int real_bytes, int by, bool walls, 
     if (by == 8) return stage_x<float, 8>(a, walls, xspec, grid, s);
   }
   return hipErrorInvalidValue;
+}
+
+template <typename Real>
+static hipError_t wide_by(const BatchArgs& a, bool walls, int grid, hipStream_t s) {
+  const dim3 block(64, 8);
+  const bool fn = a.A != 0.0;
+  if (walls && fn)
+    hipLaunchKernelGGL((wide_stage_kernel<Real, true, true>), dim3(grid), block, 0, s, a);
+  else if (walls)
+    hipLaunchKernelGGL((wide_stage_kernel<Real, true, false>), dim3(grid), block, 0, s, a);
+  else if (fn)
+    hipLaunchKernelGGL((wide_stage_kernel<Real, false, true>), dim3(grid), block, 0, s, a);
+  else
+    hipLaunchKernelGGL((wide_stage_kernel<Real, false, false>), dim3(grid), block, 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_wide(const BatchArgs& a, int real_bytes, bool walls, hipStream_t s) {
+  if (a.total_tiles < 1) return hipErrorInvalidValue;
+  return real_bytes == 8 ? wide_by<double>(a, walls, a.total_tiles, s) : wide_by<float>(a, walls, a.total_tiles, s);
 }
 
 template <typename Real, bool WALLS>

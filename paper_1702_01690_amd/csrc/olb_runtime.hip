@@ -120,8 +120,10 @@ struct Engine {
   bool walls = false;
   bool xspec = false;              // specular planes at both ends of x
   int by = 8;
+  int cus = 256;                   // compute units of the device
   bool by_set = false;             // the caller chose the tile height: the stage kernel at that height
   bool split = false;              // every stage by the split kernel (upload_desc)
+  bool wide = false;               // every stage by the 64 x 8 tile kernel (upload_desc)
   int resident = 0;                // whole steps by the resident kernel, its NG (upload_desc)
   int strip = 8;                   // tile order (BatchArgs::strip)
   int cur = 0;                     // carry index of the current f^n
@@ -182,6 +184,24 @@ struct Engine {
     return (double)ts <= std::max(800.0, per_tile * (double)tq) + (walls ? 150.0 : 0.0);
   }
 
+  // Whether 64 x 8 tiles (wide_stage_kernel) beat 63 x 8.  Tiles run to their
+  // end on the CU they start on, so a stage takes as long as the CU with the
+  // most tiles: what counts is tiles per CU, rounded up.  A 64 x 8 tile takes
+  // 5 % longer (one more face reconstruction per population).  Per stage, FP64
+  // and FP32: 512^2 2 against 3 tiles per CU, 50.6 -> 41.2 us and 33.3 -> 28.5;
+  // 1024^2 8 against 9, 178 -> 172 and 97.3 -> 93.6; 1280 x 1024 10 against 11,
+  // 217 -> 210 and 122.5 -> 119.1; 1536^2 18 against 19, 370 and 370, 216 and
+  // 212; equal counts (448^2, 768^2), 2 to 6 % slower.
+  bool wide_is_faster() const {
+    int64_t t63 = 0, t64 = 0;
+    for (const auto& q : p) {
+      t63 += tile_count(q, olbk::TILE_X, 8);
+      t64 += tile_count(q, olbk::WIDE_X, 8);
+    }
+    const int64_t per63 = (t63 + cus - 1) / cus, per64 = (t64 + cus - 1) / cus;
+    return (double)per63 >= 1.08 * (double)per64;
+  }
+
   // NG of the resident kernel that holds every instance whole, or 0
   int resident_groups() const {
     if (xspec) return 0;
@@ -199,7 +219,8 @@ struct Engine {
     int tiles = 0, blocks = 0;
     resident = by_set ? 0 : resident_groups();
     split = !by_set && !resident && split_is_faster();
-    const int tx = split ? olbk::SPLIT_X : olbk::TILE_X, ty = split ? olbk::SPLIT_Y : by;
+    wide = !by_set && !resident && !split && !xspec && by == 8 && wide_is_faster();
+    const int tx = split ? olbk::SPLIT_X : wide ? olbk::WIDE_X : olbk::TILE_X, ty = split ? olbk::SPLIT_Y : by;
     for (int i = 0; i < count(); ++i) {
       olbk::InstDesc& d = desc[i];
       d.tiles_x = (p[i].nx + tx - 1) / tx;
@@ -224,6 +245,10 @@ struct Engine {
     stream = (hipStream_t)strm;
     ws = (unsigned char*)workspace;
     ws_bytes = bytes;
+    int dev = 0, c = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && c > 0)
+      cus = c;
     rb = p[0].precision == OLB_FP32_MIXED ? 4 : 8;
     // default tile order: whole rows of tiles with FP64 storage (on the 2048^2
     // lattice 0.9 % ahead of strips of 8 tile columns), strips of 8 with FP32
@@ -506,8 +531,9 @@ struct Engine {
       ba.A = olbc::RK_A[s];
       ba.B = olbc::RK_B[s];
       ba.wguard = 0x1p-1000;
-      olb_status e = hip(split ? olbk::launch_split(ba, rb, walls, xspec, stream)
-                               : olbk::launch_stage(ba, rb, by, walls, xspec, stream), "stage kernel");
+      olb_status e = hip(split  ? olbk::launch_split(ba, rb, walls, xspec, stream)
+                         : wide ? olbk::launch_wide(ba, rb, walls, stream)
+                                : olbk::launch_stage(ba, rb, by, walls, xspec, stream), "stage kernel");
       if (e) return e;
       cur ^= 1;
     }

@@ -1,7 +1,7 @@
 """Small lattices: the kernels that update them (16 x 8 tiles split by
 velocity rows, wall ghosts formed in the tile; whole steps in one workgroup
-for lattices of up to 192 nodes) against the stage kernel, which a chosen
-tile height selects.  And the closure's gradients on small and ragged
+for lattices of up to 192 nodes) and the 64 x 8 tiles of some larger ones
+against the stage kernel, which a chosen tile height selects.  And the closure's gradients on small and ragged
 lattices.  Every node's sums are taken in the same
 order by both, so f, the moments and the wall densities agree to the bit."""
 import numpy as np
@@ -39,7 +39,11 @@ CASES = ([("noisy", s) for s in ((1, 1), (5, 3), (16, 8), (17, 9), (15, 7), (33,
          # 80, 144 and 208 places; the last that fits each and the first that does not
          + [("noisy", s) for s in ((1, 60), (64, 1), (65, 1), (8, 16), (129, 1), (3, 64), (193, 1))]
          + [("channel", s) for s in ((8, 4), (1, 160), (1, 186), (1, 187), (2, 40), (23, 3), (24, 3))]
-         + [("half", s) for s in ((1, 40), (16, 3), (7, 17))])
+         + [("half", s) for s in ((1, 40), (16, 3), (7, 17))]
+         # tiles of 64 x 8 where they put fewer on a CU: whole tiles across, a
+         # cell over eight of 63, and the last tile short of both
+         + [("noisy", s) for s in ((512, 457), (505, 483))]
+         + [("channel", (512, 461)), ("half", (510, 470))])
 
 
 def _case(kind, nx, ny):

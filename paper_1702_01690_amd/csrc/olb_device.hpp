@@ -49,7 +49,7 @@ struct InstDesc {
   double inv_ds, inv_ds3, dt, inv_tau, a, b, sigma, rho0, tref;
   float base[25];       // FP32 departure base per population: rho0 b_kx b_ky
   double tw[2], uw[2];  // lower / upper wall temperature and tangential velocity
-  int tiles_x, tiles_y; // stage tiles of 63 x BY nodes
+  int tiles_x, tiles_y; // stage tiles (of the kernel that takes the stages)
   int tile_base;        // first tile of this instance in the batch's tile queue
   int wall_block_base;  // first 64-column block of this instance (walls)
 };
@@ -86,8 +86,9 @@ constexpr int resident_places(int ng) { return 64 * ng + 16; }
 
 // One workgroup per tile of the batch's tile queue.
 hipError_t launch_stage(const BatchArgs& a, int real_bytes, int by, bool walls, bool xspec, hipStream_t s);
-// The same with 16 x 8 tiles, wall ghosts included (no launch_walls).
+// The same with 64 x 8 tiles (no specular x planes).
 hipError_t launch_wide(const BatchArgs& a, int real_bytes, bool walls, hipStream_t s);
+// The same with 16 x 8 tiles, wall ghosts included (no launch_walls).
 hipError_t launch_split(const BatchArgs& a, int real_bytes, bool walls, bool xspec, hipStream_t s);
 // nsteps whole RK-3 steps of every instance, each in one workgroup (every
 // lattice fits ng; a.stage, a.A, a.B and the tiles are unused).

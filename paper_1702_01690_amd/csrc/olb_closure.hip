@@ -216,14 +216,21 @@ constexpr int MAX_PARTS = 256;
 // every run) gets the same bits; red[0][c] holds channel c's total on return.
 // All threads of the block must call it.  (A row of four per thread and eight
 // barriers of a tree took 1 us more.)
-__device__ __forceinline__ void block_total4(const double* __restrict__ part, int nparts, double (*red)[4]) {
+// `meanwhile` issues loads that the caller needs afterwards: behind these (reads
+// return in the order of issue).
+template <typename F>
+__device__ __forceinline__ void block_total4(const double* __restrict__ part, int nparts, double (*red)[4],
+                                             F meanwhile) {
   constexpr int U = MAX_PARTS / 64;
   const int t = threadIdx.x;
   double v[U], s = 0.0;
 #pragma unroll
-  for (int j = 0; j < U; ++j) v[j] = t + j * 256 < nparts * 4 ? part[t + j * 256] : 0.0;
+  for (int j = 0; j < U; ++j) v[j] = part[min(t + j * 256, nparts * 4 - 1)];
+  __builtin_amdgcn_sched_barrier(0);
+  meanwhile();
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int j = 0; j < U; ++j) s += v[j];
+  for (int j = 0; j < U; ++j) s += t + j * 256 < nparts * 4 ? v[j] : 0.0;
 #pragma unroll
   for (int o = 4; o < 64; o <<= 1) s += __shfl_xor(s, o);
   if ((t & 63) < 4) red[t >> 6][t & 3] = s;
@@ -374,7 +381,7 @@ __global__ void __launch_bounds__(256) delta_kernel(const float* __restrict__ Z3
                                                     const double* __restrict__ part4, int nparts,
                                                     int conserve_mask, double* __restrict__ delta) {
   __shared__ double red[4][4];
-  if (conserve_mask) block_total4(part4, nparts, red);
+  if (conserve_mask) block_total4(part4, nparts, red, []() {});
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= P) return;
 #pragma unroll
@@ -691,7 +698,9 @@ static int infer_grid(int ntiles) {
 // delta[c] -= mean_c * out_scale[c] for the channels in mask; the channel
 // totals of the normalised output over P nodes are the nparts rows of
 // partial sums of infer_kernel, totalled in a fixed order by every block while
-// its first corrections are on their way.
+// its first corrections are on their way.  Every load is made, on a place that
+// is there (a channel outside the mask reads one inside it, past the end the
+// last node): behind a condition each would be waited for at once.
 template <int J>
 __global__ void __launch_bounds__(256) project_kernel(double* __restrict__ delta, int P, Norm nm,
                                                       const double* __restrict__ part4, int nparts, int mask) {
@@ -699,20 +708,18 @@ __global__ void __launch_bounds__(256) project_kernel(double* __restrict__ delta
   double v[4][J];
   auto load = [&](int p0) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+    for (int c = 0; c < 4; ++c) {
+      const double* const src = delta + (size_t)((mask >> c) & 1 ? c : __builtin_ctz(mask)) * P;
 #pragma unroll
-      for (int j = 0; j < J; ++j) {
-        const int p = p0 + j * 256;
-        v[c][j] = p < P && ((mask >> c) & 1) ? delta[(size_t)c * P + p] : 0.0;
-      }
+      for (int j = 0; j < J; ++j) v[c][j] = src[min(p0 + j * 256, P - 1)];
+    }
   };
   int p0 = blockIdx.x * (256 * J) + threadIdx.x;
-  load(p0);
-  block_total4(part4, nparts, red);
+  block_total4(part4, nparts, red, [&]() { load(p0); });
   double shift[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) shift[c] = red[0][c] / (double)P * (double)nm.out_scale[c];
-  while (p0 < P) {
+  for (;;) {
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -721,11 +728,12 @@ __global__ void __launch_bounds__(256) project_kernel(double* __restrict__ delta
         if (p < P && ((mask >> c) & 1)) delta[(size_t)c * P + p] = v[c][j] - shift[c];
       }
     p0 += gridDim.x * (256 * J);
+    if (p0 >= P) break;
     load(p0);
   }
 }
 // A node per thread up to 1024 blocks (four per CU): the shortest chain, 128^2
-// 4.1 us against 5.0 with four.  Beyond that four nodes per thread, whose loads
+// 3.9 us against 5.0 with four.  Beyond that four nodes per thread, whose loads
 // are in flight together, and still at most 1024 blocks, as each totals the
 // partial sums: 2048^2 33 us (one node per thread and a block for each 256 nodes: 41).
 static void launch_project(hipStream_t st, double* delta, int P, const Norm& nm, const double* part4, int nparts, int mask) {

@@ -60,7 +60,8 @@ def kernel_source_hash():
     h = hashlib.sha256()
     # the runtime file sets the launch configuration (tile order), which the
     # measured bytes depend on too
-    for name in ("olb_kernels.hip", "olb_split.hpp", "olb_runtime.hip", "olb_consts.hpp", "olb_device.hpp", "olb_feq.hpp"):
+    for name in ("olb_kernels.hip", "olb_split.hpp", "olb_runtime.hip", "olb_consts.hpp", "olb_device.hpp",
+                 "olb_feq.hpp"):
         with open(os.path.join(ROOT, "paper_1702_01690_amd", "csrc", name), encoding="utf-8") as fh:
             h.update(_code_only(fh.read()).encode())
     # and the compiler flags the library is built with

@@ -6,13 +6,13 @@
 // each: about 20 us from the first load to the last store, whatever the
 // lattice (FP64 32 x 32: 20.9 us a stage; the split kernel takes 8.4 us, of
 // which the loads of a tile are a third and the face reconstructions another;
-// with walls 28 against 10 us, in a box 31 against 10 us).  Here five groups of waves take the five velocity rows (ky) of a
-// tile at the same time, with every population of the tile in LDS: a thread
-// owns one node and the populations (0..4, ky), reconstructs their left and
-// lower faces, and gathers their force term from the node's 25 values.  The
-// group of row 2, which has no y faces, also takes the node's moments, force
-// and equilibrium.  Each accumulator receives its terms in the stage kernel's
-// order, so both give the same bits.
+// with walls 28 against 10 us, in a box 31 against 10 us).  Here five groups of
+// waves take the five velocity rows (ky) of a tile at the same time, with every
+// population of the tile in LDS: a thread owns one node and the populations
+// (0..4, ky), reconstructs their left and lower faces, and gathers their force
+// term from the node's 25 values.  A sixth group takes the node's moments,
+// force and equilibrium.  Each accumulator receives its terms in the stage
+// kernel's order, so both give the same bits.
 //
 // split_stage_kernel  one RK stage, 16 x 8 tiles; wall ghosts are formed in LDS
 //                     by the tiles at a wall (no wall launch)
@@ -618,7 +618,7 @@ __global__ void __launch_bounds__(SPLIT_THREADS, 6) split_stage_kernel(const Bat
 // otherwise.
 // Measured (FP64): 13 half channels of 1 x 160 nodes 44 -> 6.5 us a stage, of
 // which the faces are a third, the terms a fifth and the wall ghosts a sixth;
-// 315 waves of 20 .. 60 nodes 33 -> 3.1 us.
+// 315 waves of 20 .. 60 nodes 33 -> 3.8 us.
 // Directions one node wide have no advection and no force (every difference
 // along them is exactly zero) and are skipped.
 // Node i = y nx + x is at LDS place i, after three ghost rows with walls.

@@ -197,3 +197,18 @@ def test_restriction_factors(factor, cells):
     got = olb.restrict(fine, nx, ny, factor).cpu().numpy().reshape(4, cells[1], cells[0])
     want = cnn.restrict(m, factor)
     np.testing.assert_allclose(got, want, rtol=0, atol=(factor * factor + 16) * 2.0 ** -53 * 8 * np.abs(m).max())
+
+
+@pytest.mark.parametrize("ny", [1118, 1119])
+def test_moments_of_large_lattices(ny):
+    """The last f that is read through the caches and the first that is read
+    past them: the moments of f^eq are the fields it was formed from, up to
+    the roundings of 25 terms and as many of their sums."""
+    olb = _olb()
+    case = _noisy(1200, ny)
+    lat = olb.Lattice(case.params)
+    lat.set_fields(*case.fields)
+    tol = 50 * 2.0 ** -53 * 16 * np.abs(case.n).max()
+    for got, want in zip(lat.moments(), case.fields):
+        np.testing.assert_allclose(got.reshape(want.shape), want, rtol=0, atol=tol)
+    lat.close()

@@ -1220,7 +1220,7 @@ struct olb_closure {
   int adam_t = 0;
   int conserve_mask = 7;  // n, u_x, u_y corrections are made mean-free
   bool have_params = false;
-  float* host = nullptr;   // page-locked, NPARAM + 1: gradients and loss
+  float* host = nullptr;   // page-locked, NPARAM + 1: gradients and loss (host_buffer)
   std::string err;
 
   ~olb_closure() {
@@ -1234,6 +1234,15 @@ struct olb_closure {
     if (e == hipSuccess) return OLB_OK;
     err = std::string(what) + ": " + hipGetErrorString(e);
     return OLB_E_DEVICE;
+  }
+
+  // host, allocated by the first call that returns gradients or a loss
+  olb_status host_buffer() {
+    if (host) return OLB_OK;
+    void* p = nullptr;
+    olb_status s = hip(hipHostMalloc(&p, (NPARAM + 1) * 4, hipHostMallocDefault), "host buffer");
+    if (!s) host = static_cast<float*>(p);
+    return s;
   }
 
   // 16-pixel tiles per wave of the forward convolutions: up to FWD_MT while
@@ -1352,9 +1361,7 @@ olb_status olb_closure_init(int32_t nx, int32_t ny, void* dev_workspace, size_t 
   }
   // parameters and Adam state start at zero; every other part of the workspace
   // is written before it is read
-  olb_status s = c->hip(hipHostMalloc(reinterpret_cast<void**>(&c->host), (NPARAM + 1) * 4, hipHostMallocDefault),
-                        "host buffer");
-  if (!s) s = c->hip(hipMemsetAsync(c->ws + L.par, 0, L.w1 - L.par, c->stream), "workspace clear");
+  olb_status s = c->hip(hipMemsetAsync(c->ws + L.par, 0, L.w1 - L.par, c->stream), "workspace clear");
   if (!s) s = c->hip(hipStreamSynchronize(c->stream), "stream sync");
   if (s) {
     delete c;
@@ -1422,7 +1429,8 @@ olb_status olb_closure_gradients(olb_closure* c, const double* dev_moments, cons
                                  float* grad, float* loss) {
   if (!c || !dev_moments || !dev_reference || !grad) return OLB_E_ARG;
   if (!c->have_params) return OLB_E_STATE;
-  olb_status s = c->backward(dev_moments, dev_reference, 0.f, 0.f, 0.f, true);
+  olb_status s = c->host_buffer();
+  if (!s) s = c->backward(dev_moments, dev_reference, 0.f, 0.f, 0.f, true);
   if (!s) s = c->hip(hipStreamSynchronize(c->stream), "stream sync");
   if (s) return s;
   std::memcpy(grad, c->host, NPARAM * 4);
@@ -1437,7 +1445,8 @@ olb_status olb_closure_train_step(olb_closure* c, const double* dev_moments, con
   const int t = c->adam_t + 1;
   const float c1 = 1.0f / (1.0f - std::pow(olbk::ADAM_B1, (float)t));
   const float c2 = 1.0f / (1.0f - std::pow(olbk::ADAM_B2, (float)t));
-  olb_status s = c->backward(dev_moments, dev_reference, lr, c1, c2, loss != nullptr);
+  olb_status s = loss ? c->host_buffer() : OLB_OK;
+  if (!s) s = c->backward(dev_moments, dev_reference, lr, c1, c2, loss != nullptr);
   if (s) return s;
   c->adam_t = t;
   if (loss) {

@@ -248,13 +248,13 @@ void olb_batch_free(olb_batch* b);
  * with W[co][ci][ky][kx] weighting input (x + kx - 1, y + ky - 1).
  *
  * Moment planes are device double [4][ny][nx] (n, u_x, u_y, T), y outer.
- * A closure object holds no device memory of its own (but, from the first
- * call that returns gradients or a loss, 46 KB of page-locked host memory for
- * them): the caller's workspace
+ * A closure object holds no device memory of its own: the caller's workspace
  * (256-byte aligned, olb_closure_workspace_bytes) keeps activations,
  * parameters, Adam state and the per-workgroup partial sums of the reductions
  * over nodes.  Work is enqueued on hip_stream; calls that return host values
- * synchronise it.
+ * synchronise it.  Gradients and a training step's loss come back through a
+ * page-locked host buffer of 46 KB, of which the library keeps one for each
+ * such call that was in flight at a time, at most 16.
  * ------------------------------------------------------------------------ */
 #define OLB_CLOSURE_NPARAM 11588
 typedef struct olb_closure olb_closure;

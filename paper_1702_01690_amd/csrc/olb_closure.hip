@@ -1209,6 +1209,47 @@ CLayout clayout(int nx, int ny) {
   L.total = o;
   return L;
 }
+
+// Page-locked buffers of NPARAM + 1 floats (gradients, loss) for the calls that
+// return either: a call takes one and, once it has copied its results out,
+// leaves it for the next, of whichever object, stream, thread or GPU.  Calls
+// that run at the same time hold one each, and up to KEEP stay when none does.
+// With a buffer per object the first call of each object took 24 us longer, and
+// freeing one (27 us) waited for all work on the GPU.
+class HostBuffers {
+ public:
+  hipError_t take(float** out) {
+    {
+      std::lock_guard<std::mutex> lock(m_);
+      if (n_ > 0) {
+        *out = idle_[--n_];
+        return hipSuccess;
+      }
+    }
+    void* p = nullptr;
+    const hipError_t e = hipHostMalloc(&p, (NPARAM + 1) * sizeof(float), hipHostMallocDefault);
+    *out = static_cast<float*>(p);
+    return e;
+  }
+  // only once nothing on the GPU writes to p any more
+  void give_back(float* p) {
+    {
+      std::lock_guard<std::mutex> lock(m_);
+      if (n_ < KEEP) {
+        idle_[n_++] = p;
+        return;
+      }
+    }
+    (void)hipHostFree(p);
+  }
+
+ private:
+  static constexpr int KEEP = 16;   // 0.7 MB
+  std::mutex m_;
+  float* idle_[KEEP] = {};
+  int n_ = 0;
+};
+HostBuffers host_buffers;
 }  // namespace
 
 struct olb_closure {
@@ -1220,12 +1261,7 @@ struct olb_closure {
   int adam_t = 0;
   int conserve_mask = 7;  // n, u_x, u_y corrections are made mean-free
   bool have_params = false;
-  float* host = nullptr;   // page-locked, NPARAM + 1: gradients and loss (host_buffer)
   std::string err;
-
-  ~olb_closure() {
-    if (host) (void)hipHostFree(host);
-  }
 
   template <typename T>
   T* at(size_t off) { return reinterpret_cast<T*>(ws + off); }
@@ -1234,15 +1270,6 @@ struct olb_closure {
     if (e == hipSuccess) return OLB_OK;
     err = std::string(what) + ": " + hipGetErrorString(e);
     return OLB_E_DEVICE;
-  }
-
-  // host, allocated by the first call that returns gradients or a loss
-  olb_status host_buffer() {
-    if (host) return OLB_OK;
-    void* p = nullptr;
-    olb_status s = hip(hipHostMalloc(&p, (NPARAM + 1) * 4, hipHostMallocDefault), "host buffer");
-    if (!s) host = static_cast<float*>(p);
-    return s;
   }
 
   // 16-pixel tiles per wave of the forward convolutions: up to FWD_MT while
@@ -1298,11 +1325,11 @@ struct olb_closure {
     return hip(hipGetLastError(), "delta kernel");
   }
 
-  // The loss, in host[NPARAM] if want_loss, and with lr == 0 its gradient for
-  // every parameter, in host; with lr > 0 the Adam step of the gradients and
-  // the bf16 matrices of the new parameters.  Nothing writes to host unless
-  // the caller waits for the stream: lr == 0 or want_loss.
-  olb_status backward(const double* dev_m, const double* dev_ref, float lr, float c1, float c2, bool want_loss) {
+  // With lr == 0 the gradient for every parameter, in host, with lr > 0 the
+  // Adam step of the gradients and the bf16 matrices of the new parameters; the
+  // loss in host[NPARAM], unless host is null (lr > 0: a caller who does not
+  // wait for the stream).
+  olb_status backward(const double* dev_m, const double* dev_ref, float lr, float c1, float c2, float* host) {
     using namespace olbk;
     const float* par = at<float>(L.par);
     const int grid = infer_grid(grad_tiles(nx, ny));
@@ -1310,14 +1337,31 @@ struct olb_closure {
                 par + 32 * 4 * 9, par + (32 * 4 * 9 + 32) + 32 * 32 * 9, par + (NPARAM - 4), nx, ny,
                 at<float>(L.gpart), at<float>(L.lossp)};
     hipLaunchKernelGGL(grad_kernel, dim3(grid), dim3(64 * IW), 0, stream, ga);
-    GradSumArgs sa{at<float>(L.gpart), at<float>(L.lossp), grid, want_loss ? host : nullptr, at<float>(L.par),
-                   at<float>(L.am), at<float>(L.av), lr, c1, c2,
+    GradSumArgs sa{at<float>(L.gpart), at<float>(L.lossp), grid, host, at<float>(L.par), at<float>(L.am),
+                   at<float>(L.av), lr, c1, c2,
                    at<bf16>(L.w1), at<bf16>(L.w2), at<bf16>(L.w3), at<bf16>(L.t2), at<bf16>(L.t3)};
     if (lr > 0.f)
       hipLaunchKernelGGL(grad_sum_kernel<true>, dim3(GRAD_ROW / 64 + 1), dim3(1024), 0, stream, sa);
     else
       hipLaunchKernelGGL(grad_sum_kernel<false>, dim3(GRAD_ROW / 64 + 1), dim3(1024), 0, stream, sa);
-    return hip(hipGetLastError(), "closure backward");
+    const olb_status s = hip(hipGetLastError(), "closure backward");
+    if (!s && lr > 0.f) ++adam_t;
+    return s;
+  }
+
+  // backward for a caller who is given results: waits for them, then hands the
+  // buffer that holds them to use().  (If the wait fails the GPU may still
+  // write to the buffer, which then stays out of use.)
+  template <typename Use>
+  olb_status backward_and_wait(const double* dev_m, const double* dev_ref, float lr, float c1, float c2, Use use) {
+    float* host = nullptr;
+    olb_status s = hip(host_buffers.take(&host), "host buffer");
+    if (s) return s;
+    s = backward(dev_m, dev_ref, lr, c1, c2, host);
+    const olb_status w = hip(hipStreamSynchronize(stream), "stream sync");
+    if (!s && !w) use(host);
+    if (!w) host_buffers.give_back(host);
+    return s ? s : w;
   }
 
   olb_status pack() {
@@ -1429,13 +1473,10 @@ olb_status olb_closure_gradients(olb_closure* c, const double* dev_moments, cons
                                  float* grad, float* loss) {
   if (!c || !dev_moments || !dev_reference || !grad) return OLB_E_ARG;
   if (!c->have_params) return OLB_E_STATE;
-  olb_status s = c->host_buffer();
-  if (!s) s = c->backward(dev_moments, dev_reference, 0.f, 0.f, 0.f, true);
-  if (!s) s = c->hip(hipStreamSynchronize(c->stream), "stream sync");
-  if (s) return s;
-  std::memcpy(grad, c->host, NPARAM * 4);
-  if (loss) *loss = c->host[NPARAM];
-  return OLB_OK;
+  return c->backward_and_wait(dev_moments, dev_reference, 0.f, 0.f, 0.f, [&](const float* host) {
+    std::memcpy(grad, host, NPARAM * 4);
+    if (loss) *loss = host[NPARAM];
+  });
 }
 
 olb_status olb_closure_train_step(olb_closure* c, const double* dev_moments, const double* dev_reference,
@@ -1445,15 +1486,9 @@ olb_status olb_closure_train_step(olb_closure* c, const double* dev_moments, con
   const int t = c->adam_t + 1;
   const float c1 = 1.0f / (1.0f - std::pow(olbk::ADAM_B1, (float)t));
   const float c2 = 1.0f / (1.0f - std::pow(olbk::ADAM_B2, (float)t));
-  olb_status s = loss ? c->host_buffer() : OLB_OK;
-  if (!s) s = c->backward(dev_moments, dev_reference, lr, c1, c2, loss != nullptr);
-  if (s) return s;
-  c->adam_t = t;
-  if (loss) {
-    s = c->hip(hipStreamSynchronize(c->stream), "stream sync");
-    if (!s) *loss = c->host[NPARAM];
-  }
-  return s;
+  if (!loss) return c->backward(dev_moments, dev_reference, lr, c1, c2, nullptr);
+  return c->backward_and_wait(dev_moments, dev_reference, lr, c1, c2,
+                              [&](const float* host) { *loss = host[NPARAM]; });
 }
 
 }  // extern "C"

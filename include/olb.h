@@ -209,14 +209,17 @@ olb_status olb_batch_set_base_temperature(olb_batch* b, int32_t i, double T);
 olb_status olb_batch_set_tile_order(olb_batch* b, int32_t strip);
 /* Choose the launch configuration by timing trial_steps RK-3 steps of each
  * candidate on a uniform rest state of every instance, one parameter at a
- * time: the stage tile height (8, 16; also 12 with FP32 storage), then the
- * tile order (olb_batch_set_tile_order: rows, strips of 4, 8, 16), then,
- * when the batch replays HIP graphs (olb_batch_use_graph), the RK-3 steps
- * per graph (2, 10, 30).  None of them changes the results.  The choice is
- * read from / added to the JSON file cache_path (NULL: no cache), keyed by
- * precision, boundary kinds, instance count, total nodes and whether graphs
- * are used.  The trial overwrites the instances: set their fields
- * afterwards.  chosen_by (tile height) may be NULL. */
+ * time: the stage kernel's tile height (8, 16; also 12 with FP32 storage), then
+ * its tile order (olb_batch_set_tile_order: rows, strips of 4, 8, 16), then
+ * the kernel the batch takes by itself where that is another one
+ * (olb_set_tile), then, when the batch replays HIP graphs
+ * (olb_batch_use_graph), the RK-3 steps per graph (2, 10, 30).  None of them
+ * changes the results.  The choice is read from / added to the JSON file
+ * cache_path (NULL: no cache), keyed by precision, boundary kinds, instance
+ * count, total nodes and whether graphs are used; entries of files written
+ * before there was more than one kernel are kept in the file and not used.
+ * The trial overwrites the instances: set their fields afterwards.  chosen_by
+ * (tile height; 8 where the batch keeps its own kernel) may be NULL. */
 olb_status olb_batch_autotune(olb_batch* b, int32_t trial_steps, const char* cache_path,
                               int32_t* chosen_by);
 /* The current launch configuration: tile height, tile order (strip width,

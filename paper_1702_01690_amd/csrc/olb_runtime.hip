@@ -579,28 +579,16 @@ struct Engine {
     return OLB_OK;
   }
 
-  olb_status choose_tile(int32_t b) {
-    olb_status s = check_tile(b);
-    if (s) return s;
-    if (by_set && b == by) return OLB_OK;
-    by_set = true;
-    by = b;
-    return upload_desc();
-  }
-
-  olb_status check_tile(int32_t b) {
+  // chosen: the stage kernel at this height; otherwise (b = 8) whichever kernel
+  // upload_desc finds the fastest
+  olb_status set_tile(int32_t b, bool chosen) {
     // 12 only with FP32 storage: two 12-wave workgroups per CU fit its
     // 80-register budget, while FP64 (128 registers) would run one
     if (b != 8 && b != 16 && !(b == 12 && rb == 4))
       return fail(OLB_E_ARG, "tile height must be 8 or 16 (or 12 with FP32 storage)");
-    return OLB_OK;
-  }
-
-  olb_status set_tile(int32_t b) {
-    olb_status s = check_tile(b);
-    if (s) return s;
-    if (b == by) return OLB_OK;
+    if (b == by && chosen == by_set) return OLB_OK;
     by = b;
+    by_set = chosen;
     return upload_desc();
   }
 
@@ -633,14 +621,18 @@ struct Engine {
     long long nodes = 0;
     for (const auto& q : p) nodes += (long long)q.nx * q.ny;
     std::ostringstream k;
+    // v2: entries without it come from a search that did not know of kernels
+    // other than the stage kernel, or that timed those whatever the height
     k << (rb == 8 ? "fp64" : "fp32") << (walls ? "-walls" : "-periodic") << (xspec ? "-xspec" : "") << "-n" << count()
-      << "-nodes" << nodes << (graph_steps > 0 ? "-graphs" : "-direct");
+      << "-nodes" << nodes << (graph_steps > 0 ? "-graphs" : "-direct") << "-v2";
     return k.str();
   }
 
-  // A tuned launch configuration: tile height, tile order (strip width) and
+  // A tuned launch configuration: the stage kernel at a tile height (or, with
+  // by = 8, the automatic choice of the kernel), tile order (strip width) and
   // RK-3 steps per graph (0 when the batch launches directly).
   struct Tuning {
+    bool automatic = true;
     int by = 8, strip = 8, graph = 0;
   };
 
@@ -661,10 +653,12 @@ struct Engine {
     const size_t at = text.find("\"" + key + "\"");
     if (at == std::string::npos) return false;
     Tuning c;
-    if (!read_int(text, at, "by", c.by) || !read_int(text, at, "strip", c.strip) ||
-        !read_int(text, at, "graph", c.graph))
+    int automatic = 0;
+    if (!read_int(text, at, "auto", automatic) || !read_int(text, at, "by", c.by) ||
+        !read_int(text, at, "strip", c.strip) || !read_int(text, at, "graph", c.graph))
       return false;
-    const bool by_ok = c.by == 8 || c.by == 16 || (c.by == 12 && rb == 4);
+    c.automatic = automatic != 0;
+    const bool by_ok = c.by == 8 || (!c.automatic && (c.by == 16 || (c.by == 12 && rb == 4)));
     if (!by_ok || c.strip < 0 || c.strip > 1024 || c.graph < 0 || (c.graph > 0) != (graph_steps > 0)) return false;
     t = c;
     return true;
@@ -683,7 +677,7 @@ struct Engine {
       }
     }
     std::ostringstream entry;
-    entry << "\"" << key << "\": {\"by\": " << t.by << ", \"strip\": " << t.strip << ", \"graph\": " << t.graph
+    entry << "\"" << key << "\": {\"auto\": " << (t.automatic ? 1 : 0) << ", \"by\": " << t.by << ", \"strip\": " << t.strip << ", \"graph\": " << t.graph
           << ", \"ms_per_step\": {" << trials << "}}";
     std::string out;
     const size_t open = body.find('{'), close = body.rfind('}');
@@ -700,7 +694,7 @@ struct Engine {
   }
 
   olb_status apply_tuning(const Tuning& t) {
-    olb_status s = set_tile(t.by);
+    olb_status s = set_tile(t.by, !t.automatic);
     if (!s) s = set_tile_order(t.strip);
     if (s) return s;
     if (t.graph != graph_steps) {
@@ -730,10 +724,11 @@ struct Engine {
     return s;
   }
 
-  // Search, one parameter at a time: the tile height (8, 16, and 12 with FP32
-  // storage) in the default order, then the tile order (rows, strips of 4, 8
-  // and 16 tiles) at the best height, then, when the batch replays graphs,
-  // the steps per graph (2, 10, 30).  Results do not depend on any of them.
+  // Search, one parameter at a time: the stage kernel's tile height (8, 16, and
+  // 12 with FP32 storage) in the default order, then its tile order (rows,
+  // strips of 4, 8 and 16 tiles) at the best height, then the automatic choice
+  // where that is another kernel, then, when the batch replays graphs, the
+  // steps per graph (2, 10, 30).  Results do not depend on any of them.
   olb_status autotune(int32_t trial_steps, const char* cache_path, int32_t* chosen) {
     if (trial_steps < 1) return fail(OLB_E_ARG, "trial_steps must be >= 1");
     const std::string key = tune_key();
@@ -768,7 +763,10 @@ struct Engine {
       }
       return r;
     };
-    // direct launches while the height and order are chosen
+    // direct launches while the kernel, height and order are chosen
+    if (!s) s = set_tile(8, false);
+    const bool another = resident || split || wide;
+    best.automatic = false;
     Tuning t = best;
     t.graph = 0;
     double best_ms = 1e300;
@@ -797,8 +795,20 @@ struct Engine {
         best.strip = t.strip;
       }
     }
+    t.strip = best.strip;
+    if (another && !s) {
+      t.automatic = true;
+      t.by = 8;
+      double ms = 0.0;
+      s = run(t, "auto", ms);
+      if (!s && ms < best_ms) {
+        best.automatic = true;
+        best.by = 8;
+      }
+      t.automatic = best.automatic;
+      t.by = best.by;
+    }
     if (graphs) {
-      t.strip = best.strip;
       best_ms = 1e300;
       const int lengths[3] = {10, 2, 30};
       for (int g = 0; g < 3 && !s; ++g) {
@@ -925,7 +935,7 @@ olb_status olb_set_f(olb_ctx* c, const double* f) { return c ? c->e.set_f(0, f) 
 olb_status olb_wall_density(olb_ctx* c, double* lo, double* hi) {
   return c ? c->e.wall_density(0, lo, hi) : OLB_E_ARG;
 }
-olb_status olb_set_tile(olb_ctx* c, int32_t by) { return c ? c->e.choose_tile(by) : OLB_E_ARG; }
+olb_status olb_set_tile(olb_ctx* c, int32_t by) { return c ? c->e.set_tile(by, true) : OLB_E_ARG; }
 olb_status olb_set_base_temperature(olb_ctx* c, double T) { return c ? c->e.set_base_temperature(0, T) : OLB_E_ARG; }
 olb_status olb_set_tile_order(olb_ctx* c, int32_t strip) { return c ? c->e.set_tile_order(strip) : OLB_E_ARG; }
 olb_status olb_launch_counts(const olb_ctx* c, int32_t* stage, int32_t* walls) {
@@ -995,7 +1005,7 @@ olb_status olb_batch_use_graph(olb_batch* b, int32_t steps_per_graph) {
   b->e.graph_steps = steps_per_graph == 0 ? 0 : 2 * ((steps_per_graph + 1) / 2);
   return OLB_OK;
 }
-olb_status olb_batch_set_tile(olb_batch* b, int32_t by) { return b ? b->e.choose_tile(by) : OLB_E_ARG; }
+olb_status olb_batch_set_tile(olb_batch* b, int32_t by) { return b ? b->e.set_tile(by, true) : OLB_E_ARG; }
 olb_status olb_batch_set_base_temperature(olb_batch* b, int32_t i, double T) {
   return b ? b->e.set_base_temperature(i, T) : OLB_E_ARG;
 }

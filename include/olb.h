@@ -143,10 +143,13 @@ olb_status olb_wall_density(olb_ctx* c, double* nw_lo, double* nw_hi);
 
 /* Block height of the stage kernel: 8 (default) or 16 waves per workgroup,
  * or 12 with FP32 storage (OLB_E_ARG otherwise); each workgroup updates
- * 63 x by nodes.  Lattices and batches too small to fill the GPU with such
- * tiles take a kernel with 16 x 8 tiles instead, and those of which 64 x 8
- * tiles put fewer on a compute unit one with these, unless this call has
- * chosen a height.  Results do not depend on either (bitwise). */
+ * 63 x by nodes.  Unless this call has chosen a height, lattices and batches
+ * take another kernel where it is the faster one: too small to fill the GPU
+ * with such tiles, one with 16 x 8 tiles; where 64 x 8 tiles put fewer on a
+ * compute unit, one with these; where every lattice has at most 192 nodes (with
+ * walls, 208 with three ghost rows at each) and no specular x planes, one that
+ * holds a lattice in a workgroup and runs up to 256 whole steps in a launch.
+ * Results do not depend on any of this (bitwise). */
 olb_status olb_set_tile(olb_ctx* c, int32_t by);
 /* FP32 departure storage keeps f - rho_ref b_kx b_ky, with the per-axis base
  * b = w (1 + h(0, T - 1)) of the equilibrium at rest and temperature T
@@ -165,9 +168,10 @@ olb_status olb_set_base_temperature(olb_ctx* c, double T);
  * (bitwise).  OLB_E_ARG outside 0..1024. */
 olb_status olb_set_tile_order(olb_ctx* c, int32_t strip);
 
-/* Number of stage launches olb_step enqueues per RK-3 step (3), and of
- * wall-ghost updates (3 with walls, else 0; where the lattice takes 16 x 8
- * tiles they are part of the stage launches). */
+/* Stage updates per RK-3 step (3), and wall-ghost updates (3 with walls, else
+ * 0).  With 63 x by and 64 x 8 tiles each of them is a launch; with 16 x 8
+ * tiles the ghosts are part of the stage launches; a lattice held in a
+ * workgroup takes all of up to 256 steps in one (olb_set_tile). */
 olb_status olb_launch_counts(const olb_ctx* c, int32_t* stage, int32_t* walls);
 
 const char* olb_last_error(const olb_ctx* c);
@@ -177,9 +181,10 @@ void olb_free(olb_ctx* c);
 /* ------------------------------------------------------------------------
  * Batches: many independent instances advanced in lockstep, every RK stage
  * being ONE kernel launch over the tiles of all instances (plus one wall-
- * ghost launch with walls).  Instances may differ in every parameter except
- * precision and boundary kind.  Ownership, errors and host layouts are those
- * of the single-instance calls; i selects an instance (0 <= i < count).
+ * ghost launch with walls), or fewer (olb_launch_counts).  Instances may
+ * differ in every parameter except precision and boundary kind.  Ownership,
+ * errors and host layouts are those of the single-instance calls; i selects
+ * an instance (0 <= i < count).
  * ------------------------------------------------------------------------ */
 typedef struct olb_batch olb_batch;
 
@@ -225,7 +230,9 @@ olb_status olb_batch_autotune(olb_batch* b, int32_t trial_steps, const char* cac
 /* The current launch configuration: tile height, tile order (strip width,
  * 0 = rows) and RK-3 steps per graph (0 = direct launches). */
 olb_status olb_batch_launch_config(const olb_batch* b, int32_t* by, int32_t* strip, int32_t* steps_per_graph);
-/* Tiles per stage launch and the current tile height. */
+/* Workgroups per launch of the kernel that takes the stages, one per tile, and
+ * the tile height; one per instance (and 8) where a workgroup holds an
+ * instance whole (olb_set_tile). */
 olb_status olb_batch_tiles(const olb_batch* b, int32_t* tiles, int32_t* by);
 const char* olb_batch_last_error(const olb_batch* b);
 void olb_batch_free(olb_batch* b);

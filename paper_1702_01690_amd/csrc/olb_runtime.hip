@@ -1025,7 +1025,7 @@ olb_status olb_batch_launch_config(const olb_batch* b, int32_t* by, int32_t* str
 }
 olb_status olb_batch_tiles(const olb_batch* b, int32_t* tiles, int32_t* by) {
   if (!b || !tiles || !by) return OLB_E_ARG;
-  *tiles = b->e.total_tiles;
+  *tiles = b->e.resident ? b->e.count() : b->e.total_tiles;
   *by = b->e.by;
   return OLB_OK;
 }

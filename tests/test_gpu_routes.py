@@ -1,7 +1,9 @@
 """Which kernel a lattice takes by itself.  The tests that compare those kernels
 with the stage kernel would pass as well if the default were the stage kernel:
 here every size they use is looked up by its workgroup count, which is another
-for each kernel unless the lattice is smaller than a tile."""
+for each kernel unless the lattice is smaller than a tile.  And the tile orders
+of the kernels that have one."""
+import numpy as np
 import pytest
 
 from test_gpu_small import CASES, _case
@@ -67,3 +69,60 @@ def test_a_batch_held_in_workgroups_counts_its_instances():
     b = olb.Batch(columns + [dict(p, nx=2, ny=160)])
     assert b.tiles() == (14 * 20, 8)
     b.close()
+
+
+def _steps(case, precision, strip, by=None):
+    """f after four steps, at a tile order (None: the default) and a chosen
+    height (None: none)."""
+    olb = _olb()
+    lat = olb.Lattice(dict(case.params, precision=precision, rho_ref=2.0))
+    if by:
+        lat.set_tile(by)
+    if strip is not None:
+        lat.set_tile_order(strip)
+    lat.set_fields(*case.fields)
+    lat.step(4)
+    f = lat.get_f()
+    lat.close()
+    return f
+
+
+@pytest.mark.parametrize("precision,by", [(0, 8), (0, 16), (1, 8), (1, 12), (1, 16)])
+def test_stage_kernel_strips_visit_every_tile_once(precision, by):
+    """150 nodes are three tile columns: strips of one, of two with a narrower
+    last one, wider than the grid, and rows, on the stage kernel at each height
+    (which a chosen height selects; the default of this size has no strips)."""
+    case = _case("noisy", 150, 37)
+    ref = _steps(case, precision, None)
+    for strip in (0, 1, 2, 5, 64):
+        np.testing.assert_array_equal(_steps(case, precision, strip, by), ref, err_msg=f"strip {strip}")
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("kind,size", [("noisy", (512, 457)), ("half", (510, 470))], ids=["periodic", "half"])
+def test_wide_kernel_strips_visit_every_tile_once(kind, size, precision):
+    """Eight columns of 64 x 8 tiles: strips of one, of three with a narrower
+    last one, of the whole grid, and rows."""
+    case = _case(kind, *size)
+    ref = _steps(case, precision, None, 8)
+    for strip in (0, 1, 3, 8):
+        np.testing.assert_array_equal(_steps(case, precision, strip), ref, err_msg=f"strip {strip}")
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_stage_kernel_strips_of_a_walled_batch(precision):
+    olb = _olb()
+    cases = [_case("channel", *size) for size in ((70, 20), (40, 33), (129, 12))]
+    got = []
+    for strip in (0, 1, 2):
+        b = olb.Batch([dict(c.params, precision=precision, rho_ref=2.0) for c in cases])
+        b.set_tile(8)
+        b.set_tile_order(strip)
+        for i, c in enumerate(cases):
+            b.set_fields(i, *c.fields)
+        b.step(5)
+        got.append([b.get_f(i) for i in range(len(cases))])
+        b.close()
+    for other in got[1:]:
+        for x, y in zip(got[0], other):
+            np.testing.assert_array_equal(x, y)

@@ -174,6 +174,13 @@ struct Engine {
   // however few tiles it has, about 800 split tiles' time, where a launch of
   // the split kernel takes 9.  Walls cost the stage kernel a launch of their
   // own, 4 us.
+  // That line alone lies too far out where a split tile more than fills a round
+  // of workgroups or a stage tile hardly starts one (616 channels of 20 .. 37 x
+  // 50 .. 100, FP32: 265 against 231 us; 370 lattices of 22 .. 55 x 51 .. 102,
+  // FP64: 265 against 249).  So the times are compared as well, as 1700 batches
+  // and lattices gave them, to 6 % either way: the stage kernel's by rounds of
+  // one tile per CU, the split kernel's by two workgroups per CU.  3 % in favour
+  // of the stage kernel leaves it out in 2 of 1370 that the line lets through.
   bool split_is_faster() const {
     int64_t ts = 0, tq = 0;
     for (const auto& q : p) {
@@ -181,7 +188,13 @@ struct Engine {
       tq += tile_count(q, olbk::TILE_X, 8);
     }
     const double per_tile = rb == 8 ? 3.0 : 2.5;
-    return (double)ts <= std::max(800.0, per_tile * (double)tq) + (walls ? 150.0 : 0.0);
+    if ((double)ts > std::max(800.0, per_tile * (double)tq) + (walls ? 150.0 : 0.0)) return false;
+    const double rounds = (double)((tq + cus - 1) / cus), fill = (double)ts / (2.0 * cus);
+    const double stage_us = rb == 8 ? (walls ? 12.8 + 14.7 * rounds : 9.2 + 13.9 * rounds)
+                                    : (walls ? 14.8 + 8.5 * rounds : 11.0 + 8.0 * rounds);
+    const double split_us = rb == 8 ? (walls ? 9.3 + 11.0 * fill : 7.0 + 10.9 * fill)
+                                    : (walls ? 9.3 + 8.6 * fill : 7.3 + 7.85 * fill);
+    return split_us <= 0.97 * stage_us;
   }
 
   // Whether 64 x 8 tiles (wide_stage_kernel) beat 63 x 8.  Tiles run to their
@@ -191,7 +204,11 @@ struct Engine {
   // and FP32: 512^2 2 against 3 tiles per CU, 50.6 -> 41.2 us and 33.3 -> 28.5;
   // 1024^2 8 against 9, 178 -> 172 and 97.3 -> 93.6; 1280 x 1024 10 against 11,
   // 217 -> 210 and 122.5 -> 119.1; 1536^2 18 against 19, 370 and 370, 216 and
-  // 212; equal counts (448^2, 768^2), 2 to 6 % slower.
+  // 212; equal counts (448^2, 768^2), 2 to 6 % slower.  From seven tiles per CU
+  // on, a last round that is nearly empty ends before a tile's time has passed,
+  // and the total has to fall by most of those 5 % as well (batches with 7 to
+  // 12 against 8 to 13 tiles per CU and 1 to 3 % fewer in all: up to 1.8 %
+  // slower; up to six, 4 to 17 % faster).
   bool wide_is_faster() const {
     int64_t t63 = 0, t64 = 0;
     for (const auto& q : p) {
@@ -199,7 +216,7 @@ struct Engine {
       t64 += tile_count(q, olbk::WIDE_X, 8);
     }
     const int64_t per63 = (t63 + cus - 1) / cus, per64 = (t64 + cus - 1) / cus;
-    return (double)per63 >= 1.08 * (double)per64;
+    return (double)per63 >= 1.08 * (double)per64 && (per64 <= 6 || (double)t63 >= 1.04 * (double)t64);
   }
 
   // NG of the resident kernel that holds every instance whole, or 0

@@ -126,3 +126,28 @@ def test_stage_kernel_strips_of_a_walled_batch(precision):
     for other in got[1:]:
         for x, y in zip(got[0], other):
             np.testing.assert_array_equal(x, y)
+
+
+def _batch_route(sizes, precision):
+    """(workgroups, those of each kernel) of a periodic batch of these sizes."""
+    olb = _olb()
+    p = _case("noisy", 8, 8).params
+    b = olb.Batch([dict(p, nx=nx, ny=ny, precision=precision, rho_ref=2.0) for nx, ny in sizes])
+    got = b.tiles()[0]
+    b.close()
+    return got, {r: sum(_workgroups(r, nx, ny) for nx, ny in sizes) for r in ("split", "wide", "stage")}
+
+
+@pytest.mark.parametrize("sizes,precision,route", [
+    # three 16 x 8 tiles to one of 63 x 8, FP32 five to two: they win where the others
+    # just start another round of one per compute unit, and lose in many rounds
+    ([(40, 40)] * 110, 0, "split"), ([(40, 40)] * 600, 0, "stage"),
+    ([(30, 40), (40, 40)] * 60, 1, "split"), ([(30, 40), (40, 40)] * 250, 1, "stage"),
+    ([(30, 40)] * 600, 0, "split"), ([(30, 40)] * 600, 1, "split"),
+    # 64 x 8 tiles: 3 rounds against 4, and 10 against 11 with hardly fewer in all
+    ([(60, 320)] * 18 + [(64, 320)], 0, "wide"), ([(60, 320)] * 63 + [(64, 240)], 0, "stage"),
+    ([(60, 320)] * 63 + [(64, 240)], 1, "stage"), ([(1024, 1024)], 0, "wide"), ([(1024, 1024)], 1, "wide"),
+], ids=lambda v: f"{len(v)}x{v[0][0]}x{v[0][1]}" if isinstance(v, list) else str(v))
+def test_routes_of_batches_with_many_tiles(sizes, precision, route):
+    got, tiles = _batch_route(sizes, precision)
+    assert got == tiles[route], (got, tiles)

@@ -3,10 +3,10 @@
 // A 3-layer convolutional network (3x3 kernels, periodic padding, 4 -> 32 ->
 // 32 -> 4 channels, ReLU between layers) maps the moments (n, u_x, u_y, T) of
 // a coarse lattice to a correction of those moments.  Every convolution is an
-// implicit GEMM on the bf16 matrix cores with FP32 accumulation: forward
-// (v_mfma_f32_16x16x32_bf16, K steps of 32), backward-data (fused with the
-// ReLU mask) and backward-weight (pixel reduction) on
-// v_mfma_f32_16x16x16_bf16.  Master weights, Adam
+// implicit GEMM on the bf16 matrix cores with FP32 accumulation
+// (v_mfma_f32_16x16x32_bf16, K steps of 32): the forward layers, backward-data
+// (a forward layer on mirrored weights, with the ReLU mask) and backward-weight
+// (a reduction over pixels).  Master weights, Adam
 // moments and gradients are FP32; activations and gradients entering the
 // matrix cores are rounded to bf16 (round to nearest even).
 //

@@ -179,8 +179,9 @@ struct Engine {
   // 50 .. 100, FP32: 265 against 231 us; 370 lattices of 22 .. 55 x 51 .. 102,
   // FP64: 265 against 249).  So the times are compared as well, as 1700 batches
   // and lattices gave them, to 6 % either way: the stage kernel's by rounds of
-  // one tile per CU, the split kernel's by two workgroups per CU.  3 % in favour
-  // of the stage kernel leaves it out in 2 of 1370 that the line lets through.
+  // one tile per CU, the split kernel's by two workgroups per CU.  With 3 % in
+  // favour of the stage kernel the split kernel was the slower one in 2 of the
+  // 1370 that the line lets through.
   bool split_is_faster() const {
     int64_t ts = 0, tq = 0;
     for (const auto& q : p) {
@@ -503,8 +504,9 @@ struct Engine {
     return hip(hipStreamSynchronize(stream), "stream sync");
   }
 
-  // RK-3 steps; the resident kernel takes up to 256 in a launch (a fraction of
-  // a millisecond; more in one launch would gain less than a percent)
+  // RK-3 steps; the resident kernel takes up to 256 in a launch (2.9 ms at 315
+  // waves' 11 us a step, 4.9 ms at 13 half channels' 19; more in one launch
+  // would gain less than a percent)
   olb_status enqueue_steps(int32_t n) {
     while (n > 0) {
       const int32_t k = resident ? std::min<int32_t>(n, 256) : 1;

@@ -489,7 +489,7 @@ __global__ void __launch_bounds__(SPLIT_THREADS, 6) split_stage_kernel(const Bat
   constexpr int RB = (int)sizeof(Real);
   const uint32_t pbytes = (uint32_t)ps * RB, rbytes = (uint32_t)((ny + 5) * a.g.rs + nx) * RB;
 
-  // the tile: threads 0..319 load the even planes and n, the others the odd
+  // the tile: threads 0..383 load the even planes and n, the others the odd
   // planes and Delta p, each thread one place of every plane
   constexpr int HALF = SPLIT_THREADS / 2;
   static_assert(HALF % 64 == 0 && HALF >= SPN, "a half's waves cover a plane");
@@ -615,7 +615,11 @@ __global__ void __launch_bounds__(SPLIT_THREADS, 6) split_stage_kernel(const Bat
 // bound is the chain of one stage: sums and carry, force, terms, four barriers
 // (six with walls), with the faces beside them; the sums and the force are
 // taken by waves of their own where 1024 threads allow it (NG < 3), by row 2's
-// otherwise.
+// otherwise.  At 128 registers (above that a compute unit runs one of the
+// smaller workgroups instead of two) the FP64 forms spill a few: NG = 2 20 with
+// walls and 2 without, NG = 3 with walls 14, up to 36 bytes a lane and a handful
+// of reloads a stage; the walled forms of every NG also keep 19 to 27 scalar
+// registers in vector lanes.
 // Measured (FP64): 13 half channels of 1 x 160 nodes 44 -> 6.5 us a stage, of
 // which the faces are a third, the terms a fifth and the wall ghosts a sixth;
 // 315 waves of 20 .. 60 nodes 33 -> 3.8 us.

@@ -146,7 +146,7 @@ olb_status olb_wall_density(olb_ctx* c, double* nw_lo, double* nw_hi);
  * 63 x by nodes.  Unless this call has chosen a height, lattices and batches
  * take another kernel where it is the faster one: too small to fill the GPU
  * with such tiles, one with 16 x 8 tiles; where 64 x 8 tiles put fewer on a
- * compute unit, one with these; where every lattice has at most 192 nodes (with
+ * compute unit, one with these; where every lattice has 2 to 192 nodes (with
  * walls, 208 with three ghost rows at each) and no specular x planes, one that
  * holds a lattice in a workgroup and runs up to 256 whole steps in a launch.
  * Results do not depend on any of this (bitwise). */

@@ -220,12 +220,16 @@ struct Engine {
     return (double)per63 >= 1.08 * (double)per64 && (per64 <= 6 || (double)t63 >= 1.04 * (double)t64);
   }
 
-  // NG of the resident kernel that holds every instance whole, or 0
+  // NG of the resident kernel that holds every instance whole, or 0.  Not with a
+  // single node: that kernel skips a direction one node wide, whose force is
+  // zero as long as Delta p is finite; a Delta p that is not reaches f through
+  // the other direction, if there is one.
   int resident_groups() const {
     if (xspec) return 0;
     int ng = 1;
     for (const auto& q : p) {
       const int64_t nodes = (int64_t)q.nx * q.ny, places = nodes + (walls ? 6 * (int64_t)q.nx : 0);
+      if (nodes == 1) return 0;
       while (ng <= olbk::RESIDENT_GROUPS && (nodes > 64 * ng || places > olbk::resident_places(ng))) ++ng;
       if (ng > olbk::RESIDENT_GROUPS) return 0;
     }

@@ -624,7 +624,8 @@ __global__ void __launch_bounds__(SPLIT_THREADS, 6) split_stage_kernel(const Bat
 // which the faces are a third, the terms a fifth and the wall ghosts a sixth;
 // 315 waves of 20 .. 60 nodes 33 -> 3.8 us.
 // Directions one node wide have no advection and no force (every difference
-// along them is exactly zero) and are skipped.
+// along them is exactly zero, or not a number where Delta p is not finite, which
+// the other direction then shows) and are skipped.
 // Node i = y nx + x is at LDS place i, after three ghost rows with walls.
 template <int NG>
 struct Resident {

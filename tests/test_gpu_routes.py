@@ -27,10 +27,10 @@ def _workgroups(route, nx, ny):
 
 
 def _expected(kind, nx, ny):
-    """One workgroup holds 192 nodes, 208 with the ghost rows of two walls;
+    """One workgroup holds 2 to 192 nodes, 208 with the ghost rows of two walls;
     larger ones of a few hundred nodes a side take 16 x 8 tiles; 512 across, two
     64 x 8 tiles on each of 256 compute units instead of three 63 x 8."""
-    if not kind.startswith("box") and nx * ny <= 192 and (kind == "noisy" or nx * (ny + 6) <= 208):
+    if not kind.startswith("box") and 2 <= nx * ny <= 192 and (kind == "noisy" or nx * (ny + 6) <= 208):
         return "resident"
     return "wide" if nx > 500 else "split"
 

@@ -151,3 +151,36 @@ def _batch_route(sizes, precision):
 def test_routes_of_batches_with_many_tiles(sizes, precision, route):
     got, tiles = _batch_route(sizes, precision)
     assert got == tiles[route], (got, tiles)
+
+
+@pytest.mark.parametrize("nx,ny,box,route", [(16, 700000, False, "split"), (30, 380000, True, "split"),
+                                             (512, 22000, False, "wide")])
+def test_routes_on_plane_storage(nx, ny, box, route):
+    """Distribution arrays of more than 2^31 bytes are stored plane by plane: the
+    thin ones still take 16 x 8 tiles, others 64 x 8, with the stage kernel's
+    bits."""
+    import torch
+    olb = _olb()
+    assert 25 * nx * (ny + 6) * 8 >= 2 ** 31
+    p = dict(_case("box2" if box else "noisy", 8, 8).params, nx=nx, ny=ny)
+    fields = torch.ones(4, ny, nx, dtype=torch.float64, device="cuda:0")
+    fields[0] = 2.0 + 0.01 * torch.sin(torch.arange(nx * ny, device="cuda:0", dtype=torch.float64)).reshape(ny, nx)
+    fields[1:3] = 0.0
+    got = []
+    for by in (None, 8):
+        b = olb.Batch([p])
+        torch.cuda.synchronize()          # the batch works on a stream of its own
+        if by:
+            b.set_tile(by)
+        else:
+            assert b.tiles()[0] == _workgroups(route, nx, ny)
+        b.set_fields_device(0, fields)
+        b.step(2)
+        out = torch.empty_like(fields)
+        torch.cuda.synchronize()
+        b.moments_device(0, out)
+        b.sync()
+        got.append(out)
+        b.close()
+    assert torch.equal(*got) and torch.isfinite(got[0]).all()
+    assert not torch.equal(got[0], fields)
